@@ -49,10 +49,10 @@
  *     nothing.  Per-item length errors can only be seen on the device (the
  *     lengths live there); they give the item an all-zero slab, score -inf
  *     and a code in item_status_out.
- *   - Alignment: when S is a multiple of 4 and value is 16-byte aligned the
- *     forward pass uses 16-byte loads; other shapes take a general path with
- *     the same results.  Likewise the path writer uses 16-byte stores when S
- *     is a multiple of 16 and path_out is 16-byte aligned.
+ *   - Alignment: the forward pass uses 16-byte loads whatever S and the
+ *     alignment of value (which is that of a float at least).  The path writer
+ *     of large batches uses 16-byte stores when S is a multiple of 16 and
+ *     path_out is 16-byte aligned, bytes otherwise.
  */
 #ifndef LIBMAS_MAS_H_
 #define LIBMAS_MAS_H_

@@ -94,8 +94,12 @@ static mas_status run(const float* value, const int32_t* t_x, const int32_t* t_y
   p.NC = L.NC;
   p.EP = L.EP;
   p.NB = L.NB;
+  p.NS = L.NS;
   p.ntile = (L.T + kPathTileRows - 1) / kPathTileRows;
   p.path16 = path && (L.S % 16 == 0) && ((uintptr_t)path % 16 == 0);
+  const bool small = (uint64_t)L.B * L.T * L.S <= kEarlyMaxCells;
+  p.early = path && small;
+  p.stagger = !small;
   p.spin_limit = wait_bound();
   p.neg = sentinel;
   p.legacy = std::isfinite(sentinel) ? 1 : 0;

@@ -24,12 +24,14 @@ struct KParams {
   uint32_t* done;       // [B][NW] a wave's step masks published (tag)
   uint32_t* tmo;        // [B] a wave of the item gave up a wait in this call (tag)
   uint64_t* order;      // [B] items in the order their row_start tables were published: tag << 32 | item
-  uint64_t* slots;      // [B][NB][NC*32] boundary words of each workgroup's last wave
+  uint64_t* slots;      // [B][NS][NC*32] boundary words of each workgroup's last wave
   uint32_t* pm;         // [B][NC][EP] step masks (see mas_layout.h)
   uint8_t* pd;          // [B][NC][EP] descent bytes (see mas_layout.h)
-  int32_t B, T, S, NW, NC, EP, NB;
+  int32_t B, T, S, NW, NC, EP, NB, NS;
   int32_t ntile;        // path tiles per item: ceil(T / kPathTileRows)
   int32_t path16;       // path 16-byte aligned and S % 16 == 0
+  int32_t early;        // the sweep workgroups write the path themselves, zeros before their sweeps (small batches)
+  int32_t stagger;      // items start in the order of their lengths (large batches, see start_delay)
   int32_t spin_limit;   // bound of a device-side wait, in polls without progress
   float neg;            // value of the cells no path reaches: -inf, or the finite sentinel of the legacy mode
   int32_t legacy;       // finite sentinel (mas_forward_sentinel): triangle cells hold neg exactly
@@ -61,9 +63,9 @@ __host__ __device__ inline TraceLayout trace_layout(int B, int NW, int NC, int n
 }
 
 // Forward sweep, backtrack and (when p.path) the dense path, in one launch:
-// one 768-thread workgroup (four sweep waves, four loader waves, four
-// finisher waves) per 252 text rows of every item, then (when p.path) the
-// path-writer workgroups.
+// one 512-thread workgroup (two sweep, two loader, three finisher waves and a
+// receiver) per 126 text rows of every item, then (when p.path and not
+// p.early) the path-writer workgroups.
 hipError_t launch_mas(const KParams& p, hipStream_t stream);
 // Dense [B, T, S] u8 path from row_start [B, T+1].
 hipError_t launch_path(const int32_t* row_start, int32_t B, int32_t T, int32_t S, uint8_t* path, hipStream_t stream);

@@ -2,33 +2,39 @@
 // (Super-MAS Sec. 2, Algorithm 1; the column-parallel forward loop of
 // Algorithm 2) and the dense path writer.
 //
-// One launch computes everything (mas_kernel).  A workgroup owns 252 text
-// rows of one item and has twelve waves:
-//   * four sweep waves (one per SIMD): wave w owns 63 rows, one text row per
-//     lane in lanes 1..63, and lane 0 carries a copy of the row above the
-//     wave.  A wave walks the speech axis in chunks of 32 columns.  The
-//     diagonal predecessor Q[i-1][j-1] crosses lanes with one DPP wave_shr:1
-//     per column, crosses waves of the workgroup through LDS ring slots, and
+// One launch computes everything (mas_kernel).  A workgroup owns 126 text
+// rows of one item and has eight waves (two such workgroups fit a CU):
+//   * two sweep waves: wave w owns 63 rows, one text row per lane in lanes
+//     1..63, and lane 0 carries a copy of the row above the wave.  A wave
+//     walks the speech axis in chunks of 32 columns.  The diagonal
+//     predecessor Q[i-1][j-1] crosses lanes with one DPP wave_shr:1 per
+//     column, crosses waves of the workgroup through LDS ring slots, and
 //     crosses workgroups through 64-bit {value, tag} words in global memory.
 //     Wave g starts at chunk floor(63g / 32): every earlier cell of its rows
 //     lies in the masked triangle i > j.
-//   * four loader waves: loader w moves sweep wave w's value tiles (64 rows x
+//   * two loader waves: loader w moves sweep wave w's value tiles (64 rows x
 //     32 columns) from HBM into an LDS ring by buffer loads with the lds flag,
 //     up to four chunks ahead, and publishes each tile once it has landed.
 //     The sweep waves issue no loads of values; they read their tiles from LDS
 //     while the next chunk's reads are already in flight.
-//   * four finisher waves: finisher w turns each chunk's decision words of
-//     sweep wave w into step masks (for every row the wave owns, the columns
-//     at which the backtrack, entering the chunk in that row, moves up a row)
-//     and stores them.
+//   * three finisher waves turn the chunks' decision words into step masks
+//     (for every row the wave owns, the columns at which the backtrack,
+//     entering the chunk in that row, moves up a row) and store them.
+//   * a receiver wave brings the row above the workgroup's first row from the
+//     workgroup above (an item's first workgroup: holds back the item's start).
+// What bounds a launch: for small batches the chain of dependent steps (about
+// 0.41 us per 32 columns and 1 us per 63 rows, then the walk), for large ones
+// the reads of the value tensor (3.3 to 4 TB/s in 128-byte pieces of rows
+// 16 KiB apart) and the path's stores beside them.
 // The sweep wave holding row t_x-1 walks back from (t_x-1, t_y-1) once every
-// wave of the item has published its masks, one lookup per chunk, while the
-// four loaders of its workgroup stage the masks of upcoming chunks in LDS,
-// and publishes the item's row_start table, appending the item to the call's
-// completion order.  Path-writer workgroups, last in the grid, take
-// tiles of 32 rows of one item from a shared counter in that order and write
-// them from the table, every byte once (zeros and ones in one pass): an item
-// that finishes late is written by many workgroups at once.
+// wave of the item has published its masks, one lookup per chunk, from masks
+// or descent bytes that the other waves of its workgroup stage in LDS; all of
+// them then make the row_start table and the outputs.  The dense path: in
+// small batches (KParams::early) every workgroup zeroes its rows before its
+// sweep and the walking one writes the ones; in large batches path-writer
+// workgroups, last in the grid, take tiles of 32 rows of one item from a
+// shared counter in the order the items' tables are published and write every
+// byte once (zeros and ones in one pass).
 //
 // Every wait is bounded, and a wave only waits on waves of its own workgroup
 // or of workgroups with lower ids, which the hardware dispatches first:
@@ -156,10 +162,20 @@ struct Bound {
   uint32_t tag;
   __device__ __forceinline__ void expire();
 };
-constexpr int kLoaders = 4;          // loader waves per workgroup
-constexpr int kFinishers = 4;        // finisher waves per workgroup (step masks to memory)
-constexpr int kThreads = kThreadsPerBlock + (kLoaders + kFinishers) * kWave;
+// Waves of a workgroup by role.  The hardware deals a workgroup's waves to the
+// CU's four SIMDs in turn (waves k and k + 4 share one; probed).  Each of the
+// two sweep waves, whose column chain sets the pace, shares its SIMD with a
+// loader, which issues next to no vector ALU work; the finishers have the
+// other two SIMDs.  Three finishers serve the two sweep waves: one takes about
+// 0.47 us per chunk, one per sweep wave held the sweeps to that pace.
+enum Role { kSweep0 = 0, kFinisher0 = 2, kLoader0 = 4, kFinisher2 = 6, kReceiver = 7 };
+constexpr int kLoaders = kWavesPerBlock;    // loader waves per workgroup
+constexpr int kFinishers = 3;               // finisher waves per workgroup (step masks to memory)
+constexpr int kWaves = 8;
+constexpr int kThreads = kWaves * kWave;
 constexpr int kRing = 4;             // tile and boundary slots per sweep wave
+enum Box { kReady, kProd, kNext, kTaken, kBoxRead = kTaken + kRing, kWords = kBoxRead, kBoxWords };
+constexpr int kNever = 1 << 28;      // mailbox progress of a producer that is done
 constexpr int kPolicyDev = 16;       // cache policy sc1: device scope (write-through stores)
 constexpr int kPolicyStream = 2;     // cache policy nt: streaming, data written once and not read back
 
@@ -196,7 +212,7 @@ __host__ __device__ constexpr int swz(int r) { return (r >> 1) & 7; }
 constexpr int kWalkArea = kWavesPerBlock * kWaveRegion;
 constexpr int kMinSlots = 20;
 constexpr int kMaxSlots = 48;   // (below 64 - 10: the window addresses are kept per chunk % 64)
-constexpr int kWinLoaders = 4;  // loader waves staging windows: loader k takes chunks C-1-k, C-1-k-4, ...
+constexpr int kWinLoaders = 4;  // waves staging windows: loader k takes chunks C-1-k, C-1-k-4, ...
 constexpr int kMaxAhead = 8;    // windows in flight per loader, at most
 __host__ __device__ constexpr int rs_bytes(int T) { return ((T + 1 + kWave) * 4 + 255) & ~255; }
 __host__ __device__ constexpr int round_to(int x, int a) { return (x + a - 1) / a * a; }
@@ -221,7 +237,7 @@ struct WinGeom {
 };
 __device__ __forceinline__ WinGeom win_geom(int tx, int NW, int T) {
   const int area = kWalkArea - rs_bytes(T);
-  const int full = round_to(pd_row0(NW) + tx, 1024);
+  const int full = round_to(ent_row0(NW) + tx, 1024);
   WinGeom w;
   if (full * kMinSlots <= area) {
     w.ent = full;
@@ -244,6 +260,35 @@ __device__ __forceinline__ WinGeom win_geom(int tx, int NW, int T) {
   w.ahead = min(min(kMaxAhead, w.nslot / kWinLoaders), 63 / w.loads);
   return w;
 }
+// How an item is walked: from its step masks (kFlatMasks) or descent bytes
+// (kFlatBytes) staged whole; from a ring of blocks of four chunks' descent
+// bytes (kRing4); or, with more than about 4000 rows, from banded windows
+// (kWindows).  The walk area holds the staged bytes, then (but for windows)
+// the walk's record: the row the path enters each chunk in.
+enum WalkMode { kFlatMasks, kFlatBytes, kRing4, kWindows };
+constexpr int kBlk = 4;  // chunks of a ring block
+struct WalkPlan {
+  WalkMode mode;
+  int chunks;  // of the item
+  int bytes;   // flat: staged bytes; ring: bytes of a block (whole 1 KiB loads)
+  int blocks;  // ring: blocks
+};
+__device__ __forceinline__ WalkPlan walk_plan(int ty, int EP, int T) {
+  WalkPlan w;
+  w.chunks = (ty + kChunk - 1) / kChunk;
+  const int room = kWalkArea - rs_bytes(T) - 4 * w.chunks;
+  const int64_t bytes = (int64_t)w.chunks * EP;
+  w.blocks = 0;
+  if (4 * bytes + 1023 <= room || bytes + 1023 <= room) {
+    w.mode = 4 * bytes + 1023 <= room ? kFlatMasks : kFlatBytes;
+    w.bytes = ((int)(w.mode == kFlatMasks ? 4 * bytes : bytes) + 1023) & ~1023;
+  } else {
+    w.bytes = (kBlk * EP + 1023) & ~1023;
+    w.blocks = room / w.bytes;
+    w.mode = w.blocks >= 3 ? kRing4 : kWindows;
+  }
+  return w;
+}
 // Walker position: (chunk << 16) | row (chunk < 2048, row < 8192), or -1
 // once the walk is over.
 __device__ __forceinline__ int walk_pos(int chunk, int row) { return (chunk << 16) | row; }
@@ -257,25 +302,32 @@ struct SweepLds {
       uint8_t area[kWalkArea];  // windows from the start, row_start table at the end
     } walk;
   } u;
-  // Mailbox of sweep wave w, read with one 16-byte load per chunk:
-  //   .x ready: value tiles of chunks < ready are in w's slots (loader w);
-  //   .y prod:  boundary rows of chunks < prod are in w's slots (wave w-1);
-  //   .z cnext: progress of wave w+1: it has read every chunk < cnext, whose
+  // Mailbox of sweep wave w, read with one load per chunk (lane k: word k):
+  //   kReady:   value tiles of chunks < ready are in w's slots (kNever after
+  //             the last tile);
+  //   kProd:    boundary rows of chunks < prod are in w's slots (wave w-1, or
+  //             the receiver; kNever after their last row);
+  //   kNext:    progress of wave w+1: it has read every chunk below it, whose
   //             slots are free again (written by wave w+1);
-  //   .w taken: the finisher has read the decision words of chunks < taken
-  //             out of w's slots.
+  //   kTaken+k: the last chunk whose decision words a finisher has read out of
+  //             slot k, plus one.
+  //   kWords:   wave w-1 has left its decision words of chunks below this in
+  //             its slots (for its finishers; beside kProd, so that one write
+  //             of wave w-1 raises both).
   // Wave 0's own progress goes to cons0.
-  i32x4 box[kWavesPerBlock];
+  int box[kWavesPerBlock + 1][kBoxWords];
   int cons0;
+  int released;                 // the item may load more than its first tiles (start_item)
   int wbase[kWave];             // walk window of chunk c (lane c % 64): LDS address of row 0's descent byte
   int wmid[kWave];              // ... and of wave 0's mid entry 0 (the addresses of bytes a banded window lacks are unused)
+  int staged;                   // flat modes: waves whose part is staged
+  int bready[8];                // ring mode: staging wave k's blocks >= bready[k] are in LDS
   i32x4 wready;                 // window loader k: its windows of chunks >= wready[k] are in LDS
-  f32x4 sink[kWavesPerBlock][kChunk / 4 + 1];  // target of hand-offs nobody reads (a fixed LDS op count per step)
   int wpos;                     // walker position (walk_pos), or -1 once the walk is over
   int tile;                     // path writer: the tile taken next
   int pub;                      // path writer: the item of the tile taken (wave 0's poll), or -1
-  uint64_t bpoll[4][kChunk];    // a workgroup's first loader: the boundary words of one poll (four chunks)
-  uint32_t fdone[kWavesPerBlock];  // finisher w's step masks have all landed (the call's tag)
+  uint32_t fdone[kWavesPerBlock];  // sweep wave w's step masks have all landed (the call's tag)
+  uint32_t fcount[kWavesPerBlock]; // finishers whose part of wave w's step masks has landed
   // Row-start requests from the walker to its helper: records of up to 64
   // chunks (two buffers, request n in buffer n % 2), the chunk range they
   // cover, and the counts of requests posted and done.
@@ -284,7 +336,7 @@ struct SweepLds {
   i32x4 req_arg[2];             // base chunk, lowest and highest chunk, last request (1) or not (0)
   int req_posted, req_done;
 };
-static_assert(sizeof(SweepLds) <= 160 * 1024, "LDS");
+static_assert(sizeof(SweepLds) <= 80 * 1024, "two workgroups per CU");
 // The walk's row_start table (T + 1 entries, and up to 64 more that
 // flush_records may touch) at the end of the walk area.
 __device__ __forceinline__ int* walk_rs(SweepLds& L, int T) {
@@ -297,28 +349,6 @@ template <int N>
 __device__ __forceinline__ void vm_wait() {
   static_assert(N >= 0 && N <= 63, "vmcnt is a 6-bit counter");
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
-}
-// The same for a count known only at run time (n >= 0): waits until at most
-// k operations are outstanding for the largest k <= n of a fixed set, which
-// is at least as strict.  Compile-time branches only (a switch would become a
-// jump table read through the scalar cache on every call).
-__device__ __forceinline__ void vm_wait_le(int n) {
-  if (n >= 16) {
-    if (n >= 48) vm_wait<48>();
-    else if (n >= 32) vm_wait<32>();
-    else if (n >= 24) vm_wait<24>();
-    else vm_wait<16>();
-  } else if (n >= 4) {
-    if (n >= 12) vm_wait<12>();
-    else if (n >= 8) vm_wait<8>();
-    else if (n >= 6) vm_wait<6>();
-    else vm_wait<4>();
-  } else {
-    if (n >= 3) vm_wait<3>();
-    else if (n >= 2) vm_wait<2>();
-    else if (n >= 1) vm_wait<1>();
-    else vm_wait<0>();
-  }
 }
 // Waits until at most n operations are outstanding, n in [LO, HI] known only
 // at run time (a tree of compile-time branches).
@@ -334,13 +364,12 @@ __device__ __forceinline__ void vm_wait_exact(int n) {
       vm_wait_exact<MID + 1, HI>(n);
   }
 }
-// vm_wait_le with the call site's usual count first.
-template <int USUAL>
-__device__ __forceinline__ void vm_wait_usual(int n) {
-  if (n == USUAL)
-    vm_wait<USUAL>();
-  else
-    vm_wait_le(n);
+// Waits until at most n tiles (n in 0..3) of eight loads are outstanding.
+__device__ __forceinline__ void vm_wait_tiles(int n) {
+  if (n == 3) vm_wait<24>();
+  else if (n == 2) vm_wait<16>();
+  else if (n == 1) vm_wait<8>();
+  else vm_wait<0>();
 }
 
 __device__ __forceinline__ void Bound::expire() {
@@ -364,11 +393,13 @@ struct Cursor {
   __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc() const {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, left, kRsrcWord3);
   }
-  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_s() const {
-    const uint64_t a = (uint64_t)(uintptr_t)base;
+  // (shift: the resource starts that many bytes lower, for loads whose offsets
+  // are all larger by as much)
+  __device__ __forceinline__ __amdgpu_buffer_rsrc_t rsrc_s(uint32_t shift = 0) const {
+    const uint64_t a = (uint64_t)(uintptr_t)base - shift;
     const uint64_t lo = (uint32_t)uni((int)(uint32_t)a);
     const uint64_t hi = (uint32_t)uni((int)(uint32_t)(a >> 32));
-    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>((uintptr_t)(lo | hi << 32)), 0, uni(left), kRsrcWord3);
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<char*>((uintptr_t)(lo | hi << 32)), 0, (int)((uint32_t)uni(left) + shift), kRsrcWord3);
   }
   __device__ __forceinline__ void advance(int step) {
     base += step;
@@ -385,17 +416,22 @@ __device__ __forceinline__ Cursor make_cursor(const void* p, uint64_t bytes) {
 // dma4_dev: data written by other workgroups (device scope).
 using lds_void = __attribute__((address_space(3))) void;
 __device__ __forceinline__ lds_void* lds_at(uint32_t off) { return (lds_void*)(uintptr_t)uni((int)off); }
-__device__ __forceinline__ void dma16(uint32_t lds, __amdgpu_buffer_rsrc_t r, int voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 16, voff, 0, 0, 0);
-}
 __device__ __forceinline__ void dma16_dev(uint32_t lds, __amdgpu_buffer_rsrc_t r, int voff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 16, voff, 0, 0, kPolicyDev);
 }
 __device__ __forceinline__ void dma4_dev(uint32_t lds, __amdgpu_buffer_rsrc_t r, int voff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 4, voff, 0, 0, kPolicyDev);
 }
-__device__ __forceinline__ void dma4(uint32_t lds, __amdgpu_buffer_rsrc_t r, int voff) {
-  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds), 4, voff, 0, 0, 0);
+// The loads of one value tile (read-only input, default cache policy), load k
+// to LDS at lds + 1024 k; voff[k] is 1024 (k % 4) short (see load_tiles).
+constexpr int kTileLoads = 8;
+constexpr int kTileShift = 3072;
+template <int K = 0>
+__device__ __forceinline__ void tile_loads(uint32_t lds, __amdgpu_buffer_rsrc_t r, const int (&voff)[kTileLoads]) {
+  if constexpr (K < kTileLoads) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, lds_at(lds + 1024u * (K & ~3)), 16, voff[K], 0, 1024 * (K & 3), 0);
+    tile_loads<K + 1>(lds, r, voff);
+  }
 }
 
 // ---------------------------------------------------------------- recurrence
@@ -458,35 +494,6 @@ __device__ __forceinline__ void cols8(float& q, float& t, uint32_t& bits, float 
       : [q] "v"(q), [v0] "v"(v[0]), [v1] "v"(v[1]), [v2] "v"(v[2]), [v3] "v"(v[3]), [v4] "v"(v[4]), [v5] "v"(v[5]),
         [v6] "v"(v[6]), [v7] "v"(v[7]));
   q = o[7];
-}
-
-// One 32-column chunk for lanes 1..63 (rows row0 + lane - 1) and the carried
-// row in lane 0.  v4: this lane's 32 values (lane 0: the row above's Q);
-// qc: Q of every column (out); bits: decisions, first column in bit 31.
-// Cells of the triangle i > j hold -inf in the tile (the loader writes it
-// there): both predecessors of such a cell lie in the triangle too (lane 0's
-// copies of the row above are -inf there already), so its Q comes out
-// -inf + -inf = -inf, whatever the input held; decision bits of those cells
-// are never read.  (The first cell Q[0][0] = value[0][0] comes from row 0's
-// Q at column -1 being -0, see sweep_wave.)
-__device__ __forceinline__ void sweep_chunk(float& q, float& t, const f32x4 (&v4)[8], float (&qc)[kChunk], uint32_t& bits) {
-  float v[kChunk];
-#pragma unroll
-  for (int k = 0; k < 8; ++k) {
-    v[4 * k + 0] = v4[k].x;
-    v[4 * k + 1] = v4[k].y;
-    v[4 * k + 2] = v4[k].z;
-    v[4 * k + 3] = v4[k].w;
-  }
-  uint32_t w = 0;
-#pragma unroll
-  for (int k = 0; k < 4; ++k) {
-    float o[8];
-    cols8(q, t, w, o, v + 8 * k);
-#pragma unroll
-    for (int m = 0; m < 8; ++m) qc[8 * k + m] = o[m];
-  }
-  bits = w;
 }
 
 // First n bytes of a u64 set to 0xFF (n in [0, 8]).
@@ -586,10 +593,14 @@ __device__ __forceinline__ int wait_at_least(const int* p, int v, Bound& bd) {
   return seen;
 }
 
+// llvm.amdgcn.writelane (v_writelane_b32): lane l of `old` becomes v (v and l
+// wave-uniform), the other lanes keep theirs.
+extern "C" __device__ int mas_writelane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
+
 using lds_cchar = const __attribute__((address_space(3))) char;
 
 // The LDS reads of the next chunk in slot K of a sweep wave: the wave's
-// mailbox (ready, prod, cnext), then the lane's 8 pieces (byte offsets a[m]
+// mailbox (lane k: word k), then the lane's 8 pieces (byte offsets a[m]
 // from the base of the shared block).  The empty asm statement with a memory
 // clobber keeps the mailbox read ahead of the piece reads in issue order, and
 // one wave's LDS reads execute in issue order, so pieces that the mailbox
@@ -597,9 +608,8 @@ using lds_cchar = const __attribute__((address_space(3))) char;
 // loads for the compiler, which waits for each before its first use; callers
 // pin them ahead of the compute with a scheduling barrier.
 template <int K>
-__device__ __forceinline__ void read_ahead(lds_cchar* Lb, uint32_t box_off, const uint32_t (&a)[8], f32x4 (&v)[8],
-                                           i32x4& mb) {
-  mb = *reinterpret_cast<const __attribute__((address_space(3))) i32x4*>(Lb + box_off);
+__device__ __forceinline__ void read_ahead(lds_cchar* Lb, uint32_t box_off, const uint32_t (&a)[8], f32x4 (&v)[8], int& mb) {
+  mb = *reinterpret_cast<const __attribute__((address_space(3))) int*>(Lb + box_off);
   asm volatile("" ::: "memory");
 #pragma unroll
   for (int m = 0; m < 8; ++m)
@@ -620,50 +630,73 @@ __device__ __forceinline__ void lds_put(uint32_t addr, int v) {
                : [a] "v"(addr), [v] "v"(v)
                : "memory");
 }
-__device__ __forceinline__ void lds_put_hi8(uint32_t addr, f32x4 f) {
+// A hand-off: lanes 56..63 write f at their own addr, then lane 0 writes v to
+// the words kProd and kWords of the mailbox at box (in that order: one wave's
+// LDS operations execute in order.  Data and flag need an instruction each: a
+// wave's LDS write takes more than one pass, and another wave can read
+// between them).
+__device__ __forceinline__ void lds_hand(uint32_t addr, f32x4 f, uint32_t box, int v) {
   uint64_t sv;
-  asm volatile("s_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[m]\n\tds_write_b128 %[a], %[f]\n\ts_mov_b64 exec, %[sv]"
+  asm volatile("s_mov_b64 %[sv], exec\n\ts_mov_b64 exec, %[m]\n\tds_write_b128 %[a], %[f]\n\t"
+               "s_mov_b64 exec, 1\n\tds_write2_b32 %[b], %[v], %[v] offset0:%[o0] offset1:%[o1]\n\ts_mov_b64 exec, %[sv]"
                : [sv] "=&s"(sv)
-               : [m] "s"(0xff00000000000000ull), [a] "v"(addr), [f] "v"(f)
+               : [m] "s"(0xff00000000000000ull), [a] "v"(addr), [f] "v"(f), [b] "v"(box), [v] "v"(v), [o0] "n"((int)kProd),
+                 [o1] "n"((int)kWords)
                : "memory");
 }
 template <int N>
 __device__ __forceinline__ float dpp_row_shl(float old, float src) {
   return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(src), 0x100 | N, 0xf, 0xf, false));
 }
-// Lanes 56..63 receive lane 63's q[4k .. 4k+3] (k = lane - 56), gathered by
-// DPP row shifts inside the last 16-lane row: lane 56+k reads lane 63 with
-// row_shl:(7-k); a lane whose source lies past the end of the row keeps its
-// value, so the shifts run from the smallest up.
-__device__ __forceinline__ f32x4 gather_last_row(const float (&q)[kChunk]) {
-  f32x4 f = {q[28], q[29], q[30], q[31]};
-#define MAS_GATHER(K)                                      \
-  f.x = dpp_row_shl<7 - K>(f.x, q[4 * K + 0]);             \
-  f.y = dpp_row_shl<7 - K>(f.y, q[4 * K + 1]);             \
-  f.z = dpp_row_shl<7 - K>(f.z, q[4 * K + 2]);             \
-  f.w = dpp_row_shl<7 - K>(f.w, q[4 * K + 3]);
-  MAS_GATHER(6) MAS_GATHER(5) MAS_GATHER(4) MAS_GATHER(3) MAS_GATHER(2) MAS_GATHER(1) MAS_GATHER(0)
-#undef MAS_GATHER
-  return f;
+// Step K (0..7, in this order) of gathering lane 63's row into lanes 56..63,
+// four columns each: lane 63-K receives lane 63's q[0..3], columns 4K .. 4K+3
+// of the chunk, by a DPP row shift by K inside the last 16-lane row.  A shift
+// leaves the lanes alone whose source lies past the end of the row (63-K+1 ..
+// 63: the columns gathered before) and writes lanes below 63-K that a later
+// step overwrites.
+template <int K>
+__device__ __forceinline__ void gather_step(f32x4& f, const float* q) {
+  if constexpr (K == 0) {
+    f = f32x4{q[0], q[1], q[2], q[3]};
+  } else {
+    f.x = dpp_row_shl<K>(f.x, q[0]);
+    f.y = dpp_row_shl<K>(f.y, q[1]);
+    f.z = dpp_row_shl<K>(f.z, q[2]);
+    f.w = dpp_row_shl<K>(f.w, q[3]);
+  }
 }
+
+// Boundary words of workgroup `band` of item b.  An item has NS = ceil(NW / 4)
+// regions; workgroups r and r + NS share one (NB <= 2 NS) and tell their words
+// apart by the tag: the call's odd tag for the first, the even number after
+// it for the second.  Sharing is safe because r + NS is at least two
+// workgroups below r (with one region only workgroup 0 ever hands on): it
+// publishes a chunk only after the workgroup below r has swept that chunk
+// itself, that is, after r's words of it have been read.
+__device__ __forceinline__ uint64_t* slot_region(const KParams& p, int b, int band) {
+  return p.slots + ((size_t)b * p.NS + band % p.NS) * ((size_t)p.NC * kChunk);
+}
+__device__ __forceinline__ uint32_t slot_tag(const KParams& p, uint32_t tag, int band) { return tag + (band >= p.NS ? 1u : 0u); }
 
 // ---------------------------------------------------------------- sweep wave
 // Sweeps the wave's rows over its chunks and returns the score candidate
 // (Q at (row, t_y-1) of this lane; only meaningful for the wave holding row
-// t_x-1).  IN: where the row above the wave comes from — 0 nowhere (the wave
-// holds row 0: -inf), 1 the wave's slots and prod mailbox, filled by the
-// previous wave of the workgroup or, for wave 0 of a later workgroup, by its
-// loader from the previous workgroup's global boundary words.  OUT: 0 no
-// consumer, 1 the next wave of the workgroup, 2 global boundary words for the
-// next workgroup.
+// t_x-1).  The row above the wave comes through the wave's slots and prod
+// mailbox, filled by the previous wave of the workgroup or, for wave 0 of a
+// later workgroup, by the receiver from the previous workgroup's global
+// boundary words (for the item's first wave it is -inf in every slot and prod
+// is kNever).  OUT: 0 no consumer, 1 the next wave of the workgroup, 2 global
+// boundary words for the next workgroup.
 //
 // Step c computes chunk c from registers while the LDS reads of chunk c+1
-// (its tile, its boundary row and its mailbox) are in flight, hands the
-// chunk's last row to the consumer, and then checks the mailbox: it only
-// waits when the tile or the boundary row of chunk c+1 was not there yet.
-template <int IN, int OUT>
+// (its tile, its boundary row and the mailbox) are in flight, hands the
+// chunk's last row to the consumer, and leaves the decision words in the slot
+// for the finisher.  One vector compare of the mailbox against the four
+// progress values the step needs covers every wait; only a step that finds
+// one of them short takes the slow path.  (An earlier step with a scalar read, compare and branch per
+// mailbox word took 0.40-0.44 us against 0.24 us for the recurrence alone.)
+template <int OUT>
 __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
-  constexpr bool IN1 = IN == 1;
   const int lane = x.lane, w = x.w;
   float t = -0.0f;  // lane 0 keeps -0 for the whole sweep (see cols8)
   char* const Lc = reinterpret_cast<char*>(&L);
@@ -680,26 +713,32 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
     for (int m = 0; m < 8; ++m)
       ra[m] = lane > 0 ? wbase + (uint32_t)(r * 128 + 16 * (m ^ swz(r))) : wbase + (uint32_t)(kBoundOff + 16 * m);
   }
-  // Mailboxes: this wave's, the next wave's (OUT1: its prod), and where this
-  // wave's progress goes (the previous wave's mailbox, or cons0).
-  const uint32_t box_off = (uint32_t)((const char*)&L.box[w] - Lc);
+  // Mailboxes: this wave's (lane k reads word k), the next wave's (OUT1: its
+  // prod), and where this wave's progress goes (the previous wave's mailbox,
+  // or cons0).
+  const uint32_t box_off = (uint32_t)((const char*)&L.box[w] - Lc) + 4u * (uint32_t)min(lane, kBoxRead - 1);
   lds_cchar* const Lb = (lds_cchar*)Lc;
-  const uint32_t next_prod = lds_off(&L.box[w < kWavesPerBlock - 1 ? w + 1 : w]) + 4u;
-  const uint32_t my_cons = w > 0 ? lds_off(&L.box[w - 1]) + 8u : lds_off(&L.cons0);
-  const int* const my_box = reinterpret_cast<const int*>(&L.box[w]);
+  const uint32_t next_box = lds_off(&L.box[w + 1][0]);
+  const uint32_t my_cons = w > 0 ? lds_off(&L.box[w - 1][kNext]) : lds_off(&L.cons0);
+  const int* const my_box = L.box[w];
 
-  // Decision words: into the chunk's slot (the finisher wave turns them into
-  // step masks); a lane's word of chunk c at bits_ptr(J)[lane].
-  auto bits_ptr = [&](int k) __attribute__((always_inline)) -> uint32_t* {
-    return reinterpret_cast<uint32_t*>(Lc + wbase + (uint32_t)k * kSlotStride + kBitsOff);
-  };
-  // Global boundary words of this wave (OUT2: the last wave of workgroup
-  // g / 4): word 32c + j = {Q of the wave's last row at column 32c + j, tag}.
+  // Decision words: lane l's word of the chunk in slot k goes to byte
+  // k * kSlotStride past this (lane 0's is a scratch word).
+  const uint32_t bits_at = lds_off(Lc) + wbase + kBitsOff + 4u * (uint32_t)lane;
+  // Hand-off targets: OUT1: the boundary row of the chunk in the next wave's
+  // slot for it, lane 63-K's 16 bytes at 16 K.  OUT2: global boundary words
+  // of this wave (the last wave of workgroup g / kWavesPerBlock): word 32c + j
+  // = {Q of the wave's last row at column 32c + j, tag}; lanes outside 56..63
+  // get offsets past the resource (dropped).
+  const uint32_t hand_at = lds_off(Lc) + wbase + kWaveRegion + kBoundOff + 16u * (uint32_t)(kWave - 1 - lane);
+  const int shift = x.next_begin - x.c_begin;  // the next wave's ring position of a chunk: this wave's minus shift
   const size_t slot_words = (size_t)p.NC * kChunk;
   const __amdgpu_buffer_rsrc_t sr =
-      make_cursor(p.slots + ((size_t)x.b * p.NB + x.g / kWavesPerBlock) * slot_words, slot_words * 8u).rsrc();
+      make_cursor(slot_region(p, x.b, x.g / kWavesPerBlock), slot_words * 8u).rsrc();
+  const uint32_t stag = slot_tag(p, tag, x.g / kWavesPerBlock);
+  const int slot_voff = lane >= kWave - 8 ? 32 * (kWave - 1 - lane) : -1;
 
-  if (IN == 0) {
+  if (x.g == 0) {
     // The row above row 0 is -inf in every slot.
     if (lane < kChunk) {
 #pragma unroll
@@ -714,9 +753,9 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
   // except row 0's at column -1: -0, so that the first cell comes out as
   // -0 + value[0][0] = value[0][0] exactly (its predecessors are -0 and the
   // row above row 0, -inf in both modes: row 0 is the running sum).
-  float q = (IN == 0 && lane == 1) ? -0.0f : (IN == 0 && lane == 0) ? neg_inf() : p.neg;
-  if (IN1) wait_at_least(my_box + 1, x.c_begin, bd);
-  if (IN != 0) {
+  float q = (x.g == 0 && lane == 1) ? -0.0f : (x.g == 0 && lane == 0) ? neg_inf() : p.neg;
+  wait_at_least(my_box + kProd, x.c_begin, bd);
+  if (x.g > 0) {
     wave_lds_sync();
     const float e = bound_ptr(kRing - 1)[kChunk - 1];
     q = lane == 0 ? e : q;
@@ -727,70 +766,77 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
   // The first chunk's tile and boundary row.  Values alternate between two
   // register sets by ring position: chunk c uses set (c - c_begin) % 2.
   f32x4 va[8], vb[8];
-  wait_at_least(my_box + 0, x.c_begin + 1, bd);
-  if (IN1 && x.c_begin < x.prev_end) wait_at_least(my_box + 1, x.c_begin + 1, bd);
-  int cons_seen;  // the consumer's progress as last read (OUT1)
+  wait_at_least(my_box + kReady, x.c_begin + 1, bd);
+  wait_at_least(my_box + kProd, x.c_begin + 1, bd);
   {
-    // (Through the same inline-assembly reads as the loop: values the
-    // compiler loaded itself would make it wait for LDS inside the loop.)
-    i32x4 mb;
+    int mb;
     read_ahead<0>(Lb, box_off, ra, va, mb);
-    cons_seen = uni(mb.z);
   }
   lds_put(my_cons, x.c_begin + 1);
 
-  float qc[kChunk] = {};
+  // Lane k's need of mailbox word k at the step of chunk c: ready and prod
+  // must have passed chunk c+1 (both are kNever once their producer is done),
+  // the consumer must have read chunk c-4, and every chunk up to c-4 must have
+  // been taken by its finisher (its slot then shows c-6 or more, and c-7 or
+  // less while it has not).  Every other lane's is never short.
+  int need = lane <= kProd ? x.c_begin + 2
+             : lane == kNext ? (OUT == 1 ? x.c_begin - (kRing - 1) : -kNever)
+             : lane < kBoxRead ? x.c_begin - 2 * (kRing - 1) : -kNever;
+  constexpr uint32_t kLateRead = 1u << kReady | 1u << kProd, kLateHand = ((1u << kBoxRead) - 1u) & ~kLateRead;
+
   float score = neg_inf();
   const int row = x.g * kRowsPerWave + lane - 1;                 // this lane's text row (lanes 1..63)
   const int diag_last = (x.g * kRowsPerWave + kRowsPerWave - 1) / kChunk;  // the last chunk holding one of its diagonal cells
   Stamps stamps;  // (debug build) lane k: chunk 8k+7 (or the last chunk) done
   const int m_last = (x.ty - 1) % kChunk;
 
-  // The last row of chunk cp (in lane 63's qc) for the next wave, right
-  // after its compute: gathered into lanes 56..63 (four columns each).  OUT1:
-  // one LDS write into the next wave's slot for chunk cp (once it has read
-  // chunk cp-4 from that slot), then its mailbox's prod.  Chunks the next
-  // wave does not read (cp < next_begin - 1) go to this wave's sink, so that
-  // every step issues the same LDS operations and the compiler's waits stay
-  // exact.  OUT2: two device-scope 16-byte stores per lane of {value, tag}
-  // pairs; lanes outside 56..63 get offsets past the resource (dropped).
-  const uint32_t sink = lds_off(&L.sink[w][0]);
-  auto hand_off = [&](int cp) __attribute__((always_inline)) {
-    const bool real = cp >= x.next_begin - 1;
-    if (OUT == 1) {
-      if (real && cons_seen < cp - (kRing - 1)) cons_seen = wait_at_least(my_box + 2, cp - (kRing - 1), bd);
-      const int kn = (cp - x.next_begin) & (kRing - 1);
-      const uint32_t ns = real ? wbase + kWaveRegion + (uint32_t)kn * kSlotStride + kBoundOff : sink;
-      lds_put_hi8(ns + 16u * (uint32_t)(lane - (kWave - 8)), gather_last_row(qc));
-      lds_put(real ? next_prod : sink + 128u, cp + 1);
-    } else if (OUT == 2 && real) {
-      const f32x4 f = gather_last_row(qc);
-      const bool mine = lane >= kWave - 8;
-      const int o = cp * (kChunk * 8) + 32 * (lane - (kWave - 8));
-      const u32x4 lo = {__float_as_uint(f.x), tag, __float_as_uint(f.y), tag};
-      const u32x4 hi = {__float_as_uint(f.z), tag, __float_as_uint(f.w), tag};
-      __builtin_amdgcn_raw_buffer_store_b128(lo, sr, mine ? o : -1, 0, kPolicyDev);
-      __builtin_amdgcn_raw_buffer_store_b128(hi, sr, mine ? o + 16 : -1, 0, kPolicyDev);
-    }
-  };
-
   // Chunk c at ring position J = (c - c_begin) % kRing, its values in vc,
   // the next chunk's read into vn.
   auto step = [&](auto pos_c, int c, f32x4 (&vc)[8], f32x4 (&vn)[8]) __attribute__((always_inline)) {
     constexpr int J = decltype(pos_c)::value;
     constexpr int J1 = (J + 1) & (kRing - 1);
-    const bool has_next = c + 1 < x.c_end;
-    const bool need_prod = IN1 && c + 1 < x.prev_end;
     // Reads of chunk c+1, in flight during the compute of chunk c: the
     // mailbox first, then the values (one LDS queue per wave: in order).
     // After the last chunk they read the next slot's stale contents, unused.
-    i32x4 mb;
+    int mb;
     read_ahead<J1>(Lb, box_off, ra, vn, mb);
     __builtin_amdgcn_sched_barrier(0);
 
-    uint32_t bits = 0;
-    sweep_chunk(q, t, vc, qc, bits);
-    __builtin_amdgcn_sched_barrier(0);
+    // Cells of the triangle i > j hold -inf in the tile (the loader writes it
+    // there): both predecessors of such a cell lie in the triangle too (lane
+    // 0's copies of the row above are -inf there already), so its Q comes out
+    // -inf + -inf = -inf, whatever the input held; decision bits of those
+    // cells are never read.  (The first cell Q[0][0] = value[0][0] comes from
+    // row 0's Q at column -1 being -0.)
+    uint32_t bits = 0, late;
+    f32x4 hand;
+    const bool last = c == x.c_end - 1;
+    auto quarter = [&](auto k_c) __attribute__((always_inline)) {
+      constexpr int k = decltype(k_c)::value;
+      const float v[8] = {vc[2 * k].x, vc[2 * k].y, vc[2 * k].z, vc[2 * k].w,
+                          vc[2 * k + 1].x, vc[2 * k + 1].y, vc[2 * k + 1].z, vc[2 * k + 1].w};
+      float o[8];
+      cols8(q, t, bits, o, v);
+      if (OUT == 0) {
+        if (last) {
+#pragma unroll
+          for (int m = 0; m < 8; ++m) score = (8 * k + m == m_last) ? o[m] : score;
+        }
+      } else {
+        gather_step<2 * k>(hand, o);
+        gather_step<2 * k + 1>(hand, o + 4);
+      }
+    };
+    quarter(std::integral_constant<int, 0>());
+    // The mailbox read has arrived.  If the reads of chunk c+1 were not too
+    // early, its slot is free for the next tile and boundary row now (this
+    // write executes after them), most of a step before its values are used.
+    late = (uint32_t)__builtin_amdgcn_ballot_w64(need > mb);
+    need += 1;
+    if (__builtin_expect((late & kLateRead) == 0u, 1)) lds_put(my_cons, c + 2);
+    quarter(std::integral_constant<int, 1>());
+    quarter(std::integral_constant<int, 2>());
+    quarter(std::integral_constant<int, 3>());
     if (p.legacy && c <= diag_last) {
       // Legacy mode: the backtrack steps up at i == j whatever Q says (the
       // stay candidate is a masked cell); with a finite sentinel the
@@ -798,32 +844,36 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
       const int rel = row - c * kChunk;
       bits |= (lane > 0 && rel >= 0 && rel < kChunk) ? 1u << (kChunk - 1 - rel) : 0u;
     }
-    hand_off(c);
-    // The slot's decision words of chunk c-4 must have been taken (mailbox
-    // .w, read with this step's mailbox; rarely not yet).
-    if (uni(mb.w) < c - (kRing - 1)) {
-      wait_at_least(my_box + 3, c - (kRing - 1), bd);
+    // The slot of the consumer and the slot's words of chunk c-4 (rarely not
+    // free yet).
+    if (__builtin_expect((late & kLateHand) != 0u, 0)) {
+      if (OUT == 1) wait_at_least(my_box + kNext, c - (kRing - 1), bd);
+      wait_at_least(my_box + kTaken + J, c - (kRing - 1), bd);
+    }
+    *(__attribute__((address_space(3))) uint32_t*)(uintptr_t)(bits_at + (uint32_t)(J * kSlotStride)) = bits;
+    // (Chunks before next_begin - 1 are handed on too, though the next wave
+    // does not read them: their slots' rows are overwritten before it does.)
+    if (OUT == 1) {
+      lds_hand(hand_at + (uint32_t)(((J - shift) & (kRing - 1)) * kSlotStride), hand, next_box, c + 1);
+    } else {
+      if (OUT == 2) {
+        const u32x4 lo = {__float_as_uint(hand.x), stag, __float_as_uint(hand.y), stag};
+        const u32x4 hi = {__float_as_uint(hand.z), stag, __float_as_uint(hand.w), stag};
+        __builtin_amdgcn_raw_buffer_store_b128(lo, sr, slot_voff, c * (kChunk * 8), kPolicyDev);
+        __builtin_amdgcn_raw_buffer_store_b128(hi, sr, slot_voff < 0 ? -1 : slot_voff + 16, c * (kChunk * 8), kPolicyDev);
+      }
+      lds_put(next_box + 4u * kWords, c + 1);
+    }
+    if (__builtin_expect((late & kLateRead) != 0u, 0)) {
+      // The reads of chunk c+1 were too early: wait for the tile and the
+      // boundary row, and read again.
+      wait_at_least(my_box + kReady, c + 2, bd);
+      wait_at_least(my_box + kProd, c + 2, bd);
+      read_ahead<J1>(Lb, box_off, ra, vn, mb);
+      lds_put(my_cons, c + 2);
       lgkm_wait0();
     }
-    bits_ptr(J)[lane] = bits;
-    if (OUT == 0 && c == x.c_end - 1) {
-#pragma unroll
-      for (int m = 0; m < kChunk; ++m) score = (m == m_last) ? qc[m] : score;
-    }
-
-    if (has_next) {
-      // The reads of chunk c+1 are usable if the tile and the boundary row
-      // were there when they were issued; otherwise wait and read again.
-      if (OUT == 1) cons_seen = max(cons_seen, uni(mb.z));
-      if (uni(mb.x) < c + 2 || (need_prod && uni(mb.y) < c + 2)) {
-        wait_at_least(my_box + 0, c + 2, bd);
-        if (need_prod) wait_at_least(my_box + 1, c + 2, bd);
-        read_ahead<J1>(Lb, box_off, ra, vn, mb);
-        lgkm_wait0();
-      }
-      lds_put(my_cons, c + 2);
-    }
-    if ((c & 7) == 7 || c == x.c_end - 1) stamps.at(c >> 3);
+    if ((c & 7) == 7 || last) stamps.at(c >> 3);
   };
   for (int c = x.c_begin; c < x.c_end; c += kRing) {
     step(std::integral_constant<int, 0>(), c, va, vb);
@@ -831,9 +881,8 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
     if (c + 2 < x.c_end) step(std::integral_constant<int, 2>(), c + 2, va, vb);
     if (c + 3 < x.c_end) step(std::integral_constant<int, 3>(), c + 3, vb, va);
   }
-  // Every chunk's decision words are in the slots (the finisher takes chunk
-  // c once this progress passes c + 1).
-  lds_put(my_cons, x.c_end + 1);
+  // The next wave needs no boundary rows from here on.
+  if (OUT == 1) lds_put(next_box + 4u * kProd, kNever);
   stamps.flush(trace_of(p).chunk + ((size_t)x.b * p.NW + x.g) * kWave);
   vm_wait<0>();
   return score;
@@ -849,12 +898,15 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
 // Estimates are in wall-clock ticks (100 MHz): kTicksPerChunk per 32
 // columns (about one chunk step of a sweep wave in a full batch) and
 // kTicksPerGroup per 63 rows, chosen by timing full batches of mixed lengths
-// (a per-wave term close to a wave's own start lag, about 270 ticks, delays
-// items with few rows too long).  Batches larger than kDelayMaxBatch start
+// (five draws of B = 64, T = 1024, S = 4096: 168 us on average, against 170
+// to 174 us with 85 / 100, 60 / 200, 120 / 180 or 130 / 130 ticks).  Small batches (KParams::stagger)
+// start at once: they do not fill HBM, and a delay made from a full batch's
+// steps would turn short items into the last ones (32 x 256 x 1024, ragged:
+// 38.9 us with delays, 33.5 us without).  Batches larger than kDelayMaxBatch start
 // at once (every workgroup would read every length), and no delay exceeds
 // kDelayMaxTicks (1 ms, far below the bound of any device-side wait).
-constexpr int kTicksPerChunk = 85;
-constexpr int kTicksPerGroup = 100;
+constexpr int kTicksPerChunk = 110;
+constexpr int kTicksPerGroup = 130;
 constexpr int kDelayPercent = 80;
 constexpr int kDelayMaxBatch = 1024;
 constexpr int kDelayMaxTicks = 100000;
@@ -866,13 +918,27 @@ __device__ __forceinline__ int est_ticks(int tx, int ty, int T, int S) {
 
 // Start delay of item b in ticks (wave-uniform).
 __device__ __forceinline__ int start_delay(const KParams& p, int b, int lane) {
-  if (p.B > kDelayMaxBatch) return 0;
+  if (!p.stagger || p.B > kDelayMaxBatch) return 0;
   int m = 0;
   for (int i = lane; i < p.B; i += kWave) m = max(m, est_ticks(p.t_x[i], p.t_y[i], p.T, p.S));
 #pragma unroll
   for (int off = kWave / 2; off >= 1; off >>= 1) m = max(m, __shfl_xor(m, off));
   const int mine = est_ticks(p.t_x[b], p.t_y[b], p.T, p.S);
   return uni(min((m - mine) / 100 * kDelayPercent, kDelayMaxTicks));
+}
+
+// The item's first workgroup: releases the item once its delay is over.  A
+// wave with nothing else to do computes the delay (four dependent memory
+// round trips) beside the loads of the item's first tiles; in the loader
+// itself they completed behind those (the first tile was published 8.3 us
+// after the workgroup's start instead of 4.6 us, B = 32).
+__device__ __forceinline__ void start_item(const KParams& p, SweepLds& L, int b, int lane) {
+  const int delay = start_delay(p, b, lane);
+  if (delay > 0) {
+    const uint64_t until = wall_clock64() + (uint64_t)delay;
+    while (wall_clock64() < until) __builtin_amdgcn_s_sleep(127);
+  }
+  lds_put(lds_off(&L.released), 1);
 }
 
 // ---------------------------------------------------------------- loader wave
@@ -915,144 +981,146 @@ __device__ __forceinline__ void mask_tile(const KParams& p, uint32_t slot, int g
 
 // Value tiles of sweep wave w, chunks [c_begin, c_end), each into the slot
 // its sweep wave has handed back; tiles that cross the triangle i > j get
-// -inf there (mask_tile) before they are published.  ALIGNED (value 16-byte aligned, S % 4 ==
-// 0): lane L of load k (k = 0..7) fetches tile row 8k + L/8, piece
-// (L % 8) ^ swz(row), so each load covers eight 128-byte row segments and
-// lands as eight contiguous swizzled LDS rows; up to kRing tiles in flight.
-// Otherwise 4-byte loads of the same layout, one tile in flight.
-//
-// BOUND (the loader of wave 0 of every workgroup but an item's first): the
-// sweep wave's boundary rows too.  The previous workgroup's last wave
-// publishes Q of its last row as {value, tag} words in global memory; the
-// loader polls four chunks per round trip (two chunks per device-scope
-// load), and once a chunk's 32 words all carry this call's tag and its ring
-// slot is free, moves the values into the slot's boundary row and raises the
-// sweep wave's prod, as a wave of the same workgroup would.  So the sweep wave waits on LDS only: none of its
-// steps waits for a global load (which would also wait for its own
-// write-through stores).
-template <bool ALIGNED, bool BOUND>
-__device__ __forceinline__ void load_tiles(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
+// -inf there (mask_tile) before they are published.  Lane l of load k
+// (k = 0..7) fetches tile row 8k + l/8, piece (l % 8) ^ swz(row), so each
+// load covers eight 128-byte row segments and lands as eight contiguous
+// swizzled LDS rows; up to kRing tiles in flight.  Rows need not be 16-byte
+// aligned: a 16-byte buffer load takes any 4-byte aligned address and is
+// range-checked word by word (probed), so odd S and value pointers take the
+// same path.  (They took 4-byte loads, one tile in flight, before.)
+__device__ __forceinline__ void load_tiles(const KParams& p, SweepLds& L, const WaveCtx& x, Bound& bd) {
   const int lane = x.lane, w = x.w;
   const float* slab = p.value + (size_t)x.b * (size_t)p.T * (size_t)p.S;
   const uint64_t slab_bytes = (uint64_t)p.T * (uint64_t)p.S * 4u;
   Cursor vr = make_cursor(slab, slab_bytes);
   vr.advance((int)((uint64_t)x.g * kRowsPerWave * (uint64_t)p.S * 4u) + x.c_begin * (kChunk * 4));
   const uint32_t ring = lds_off(&L.u.ring[w][0]);
-  constexpr int kOps = ALIGNED ? 8 : 32;  // loads per tile
-  constexpr int kInflight = ALIGNED ? kRing : 1;
-  // Per-lane byte offsets, relative to the chunk's first tile row; rows past
-  // 2^31 bytes fall outside every resource.
-  int voff[kOps];
+  // Every fourth load sets the LDS address; the next three add 1 KiB each by
+  // the instruction's offset, which the memory address gets too: the resource
+  // starts 3 KiB below the tile and the per-lane offsets make up for it.  (A
+  // wave that set the LDS address for every load took 0.38-0.40 us per tile,
+  // 0.31-0.33 us this way, whether two, four or seven tiles were in flight:
+  // a wave has about 16 loads in flight at most.)  Offsets past 2^31 bytes
+  // fall outside every resource.
+  int voff[kTileLoads];
 #pragma unroll
-  for (int k = 0; k < kOps; ++k) {
-    const int r = ALIGNED ? 8 * k + (lane >> 3) : 2 * k + (lane >> 5);
-    const int pos = ALIGNED ? (lane & 7) : ((lane & 31) >> 2);
-    const uint32_t elem = ALIGNED ? 0u : 4u * (uint32_t)(lane & 3);
-    const uint64_t o = (uint64_t)r * (uint64_t)p.S * 4u + 16u * (uint32_t)(pos ^ swz(r)) + elem;
-    voff[k] = o < 0x80000000ull ? (int)o : (int)0x80000000u;
+  for (int k = 0; k < kTileLoads; ++k) {
+    const int r = 8 * k + (lane >> 3);
+    const uint64_t o = (uint64_t)r * (uint64_t)p.S * 4u + 16u * (uint32_t)((lane & 7) ^ swz(r));
+    voff[k] = (int)((o < 0x80000000ull ? (uint32_t)o : 0x90000000u) + kTileShift - 1024u * (k & 3));
   }
   int issued = x.c_begin, readied = x.c_begin;
-  bool held = x.g != 0;  // the item's first group waits for its start once its first tiles are in flight
+  // The item's first wave gets no more than its first tiles until the item is
+  // released (start_item).
+  bool held = x.g == 0;
   // The sweep wave's progress (its slots below it are free again).
-  const int* const progress = w > 0 ? reinterpret_cast<const int*>(&L.box[w - 1]) + 2 : &L.cons0;
-  const uint32_t ready_addr = lds_off(&L.box[w]);
+  const int* const progress = w > 0 ? &L.box[w - 1][kNext] : &L.cons0;
+  const uint32_t ready_addr = lds_off(&L.box[w][kReady]);
   int cons = x.c_begin - 1;
-  // BOUND: chunks bnext .. bend-1 still to deliver (from c_begin-1, which the
-  // previous wave always computes).
-  int bnext = x.c_begin - 1;
-  const int bend = BOUND ? x.prev_end : bnext;
-  // (the boundary words of the previous workgroup's last wave)
-  const uint64_t* const bsrc = p.slots + ((size_t)x.b * p.NB + (x.g > 0 ? x.g / kWavesPerBlock - 1 : 0)) * ((size_t)p.NC * kChunk);
-  const uint32_t prod_addr = lds_off(&L.box[w]) + 4u;
-  const __amdgpu_buffer_rsrc_t brs = make_cursor(bsrc, (uint64_t)p.NC * kChunk * 8u).rsrc_s();
-  const uint32_t bpoll_lds = lds_off(&L.bpoll[0][0]);
-  int bspins = 0;
-  // Issue while slots are free (the slot of chunk c held chunk c-4).
-  auto issue_tiles = [&]() __attribute__((always_inline)) {
-    while (issued < x.c_end && issued - readied < kInflight) {
+  while (readied < x.c_end && !bd.out) {
+    // Issue while slots are free (the slot of chunk c held chunk c-4).
+    // (Two tiles until the first has landed: the wave's loads are issued in
+    // order, about 16 in flight, so more would only hold up the first.)
+    while (issued < x.c_end && issued - readied < (readied == x.c_begin ? 2 : kRing)) {
+      if (held && issued >= kRing) {
+        held = uni(lds_poll(&L.released)) == 0;
+        if (held) break;
+      }
       if (issued > cons + kRing - 1) {
         cons = uni(lds_poll(progress));
         if (issued > cons + kRing - 1) break;
       }
-      const __amdgpu_buffer_rsrc_t r = vr.rsrc_s();
-      const uint32_t dst = ring + (uint32_t)((issued - x.c_begin) & (kRing - 1)) * kSlotStride;
-#pragma unroll
-      for (int k = 0; k < kOps; ++k) {
-        if (ALIGNED)
-          dma16(dst + 1024u * k, r, voff[k]);
-        else
-          dma4(dst + 256u * k, r, voff[k]);
-      }
+      tile_loads(ring + (uint32_t)((issued - x.c_begin) & (kRing - 1)) * kSlotStride, vr.rsrc_s(kTileShift), voff);
       vr.advance(kChunk * 4);
       ++issued;
     }
-  };
-  while ((readied < x.c_end || bnext < bend) && !bd.out) {
-    issue_tiles();
-    if (!held) {
-      held = true;
-      const int delay = start_delay(p, x.b, lane);
-      if (delay > 0) {
-        const uint64_t until = wall_clock64() + (uint64_t)delay;
-        while (wall_clock64() < until) __builtin_amdgcn_s_sleep(127);
-      }
-    }
-    if (BOUND && bnext < bend) {
-      if (bnext > cons + kRing - 1) cons = uni(lds_poll(progress));
-      if (bnext <= cons + kRing - 1) {
-        // The words of chunks c0 .. c0 + 3 (1 KiB, lane l: 16 bytes) into
-        // LDS by one load past the caches, then the tiles for the slots that
-        // are free now.  Loads complete in order, so waiting until only
-        // those tiles are outstanding covers the poll and every tile before
-        // it, and keeps the new tiles in flight: a poll does not drain the
-        // loader's pipeline.  Words past the workgroup's region read as 0
-        // (never a call's tag).
-        const int c0 = bnext;
-        dma16_dev(bpoll_lds, brs, c0 * (kChunk * 8) + 16 * lane);
-        const int before = issued;
-        issue_tiles();
-        vm_wait_le(kOps * (issued - before));
-        if (readied < before) {
-          for (; readied < before; ++readied)
-            if (readied < x.mask_end) mask_tile(p, ring + (uint32_t)((readied - x.c_begin) & (kRing - 1)) * kSlotStride, x.g, readied, lane);
-          lds_put(ready_addr, readied);
-        }
-#pragma unroll
-        for (int h = 0; h < 4; ++h) {
-          const int c = c0 + h;
-          const uint64_t wd = L.bpoll[h][lane & (kChunk - 1)];
-          const uint64_t stale = __builtin_amdgcn_ballot_w64((uint32_t)(wd >> 32) != tag);
-          if (bnext != c || c >= bend || c > cons + kRing - 1 || (uint32_t)stale != 0u) break;
-          float* const brow = reinterpret_cast<float*>(reinterpret_cast<char*>(&L.u.ring[w][0]) +
-                                                       ((c - x.c_begin) & (kRing - 1)) * kSlotStride + kBoundOff);
-          if (lane < kChunk) brow[lane] = __uint_as_float((uint32_t)wd);
-          lds_put(prod_addr, c + 1);
-          ++bnext;
-        }
-        if (bnext == c0) {
-          // Not published yet.
-          if (++bspins > bd.limit) bd.expire();
-          __builtin_amdgcn_s_sleep(1);
-        } else {
-          bspins = 0;
-        }
-        continue;
-      }
-    }
     if (issued == readied) {
       // Nothing in flight and no free slot: wait for the sweep wave.
-      const int need = BOUND && bnext < bend ? min(issued, bnext) : issued;
-      cons = wait_at_least(progress, need - (kRing - 1), bd);
+      if (held) {
+        wait_at_least(&L.released, 1, bd);
+        held = false;
+      }
+      cons = wait_at_least(progress, issued - (kRing - 1), bd);
       continue;
     }
     // The oldest tile in flight has landed once at most the younger ones
     // are outstanding.
-    vm_wait_usual<kOps * (kInflight - 1)>(kOps * (issued - readied - 1));
+    vm_wait_tiles(issued - readied - 1);
     if (readied < x.mask_end) mask_tile(p, ring + (uint32_t)((readied - x.c_begin) & (kRing - 1)) * kSlotStride, x.g, readied, lane);
     ++readied;
-    lds_put(ready_addr, readied);
+    lds_put(ready_addr, readied < x.c_end ? readied : kNever);
   }
   vm_wait<0>();
+}
+
+// ---------------------------------------------------------------- receiver wave
+// The boundary rows of a workgroup's first sweep wave (of every workgroup but
+// an item's first).  The previous workgroup's last wave publishes Q of its
+// last row as {value, tag} words in global memory; the receiver polls four
+// chunks per device-scope load (lane l: the words of two columns), two loads
+// in flight, and moves the rows of the leading chunks whose 32 words all
+// carry this call's tag into their ring slots, as far as those are free, and
+// raises the sweep wave's prod, as a wave of the same workgroup would.  So
+// the sweep wave waits on LDS only.  (A wave of its own: a loader's polls
+// complete in order with its tile loads, and each cost a memory round trip of
+// the tiles: a workgroup ran 2.7 us behind the one above it, 0.06 us per
+// chunk slower.)  Words past the workgroup's region read as 0 (never a tag).
+__device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
+  const int lane = x.lane;
+  const int band = x.g / kWavesPerBlock - 1;  // the workgroup above
+  const uint32_t stag = slot_tag(p, tag, band);
+  const __amdgpu_buffer_rsrc_t r = make_cursor(slot_region(p, x.b, band), (uint64_t)p.NC * kChunk * 8u).rsrc_s();
+  const uint32_t prod_addr = lds_off(&L.box[0][kProd]);
+  const uint32_t ring = lds_off(&L.u.ring[0][0]) + kBoundOff + 8u * (uint32_t)(lane & 15);
+  int next = x.c_begin - 1, cons = x.c_begin - 1, spins = 0;
+  const int end = x.prev_end;
+  auto poll = [&](int c0) __attribute__((always_inline)) -> u32x4 {
+    return __builtin_amdgcn_raw_buffer_load_b128(r, 16 * lane, c0 * (kChunk * 8), kPolicyDev);
+  };
+  // Delivers what a poll from chunk c0 on holds past `next`.
+  auto deliver = [&](int c0, u32x4 wd) __attribute__((always_inline)) {
+    const uint64_t ok = __builtin_amdgcn_ballot_w64(wd.y == stag && wd.w == stag);
+    int n = 0;  // leading chunks of the poll that are whole
+    if ((uint32_t)(ok & 0xffffu) == 0xffffu) {
+      n = 1;
+      if ((uint32_t)(ok >> 16 & 0xffffu) == 0xffffu) {
+        n = 2;
+        if ((uint32_t)(ok >> 32 & 0xffffu) == 0xffffu) {
+          n = 3;
+          if ((uint32_t)(ok >> 48) == 0xffffu) n = 4;
+        }
+      }
+    }
+    int to = min(c0 + n, end);
+    if (to > next && to - 1 > cons + kRing - 1) {
+      cons = uni(lds_poll(&L.cons0));
+      to = min(to, cons + kRing);
+    }
+    if (to > next) {
+      const int c = c0 + (lane >> 4);
+      if (c >= next && c < to)
+        *(__attribute__((address_space(3))) uint64_t*)(uintptr_t)(ring + (uint32_t)(((c - x.c_begin) & (kRing - 1)) * kSlotStride)) =
+            (uint64_t)wd.x | (uint64_t)wd.z << 32;
+      next = to;
+      lds_put(prod_addr, next < end ? next : kNever);
+      spins = 0;
+    } else {
+      if (++spins > bd.limit) bd.expire();
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+  if (next >= end) lds_put(prod_addr, kNever);
+  int ca = next;
+  u32x4 a = poll(ca);
+  while (next < end && !bd.out) {
+    const int cb = next;
+    const u32x4 b = poll(cb);
+    deliver(ca, a);
+    if (next >= end) break;
+    ca = next;
+    a = poll(ca);
+    deliver(cb, b);
+  }
 }
 
 // ---------------------------------------------------------------- step masks
@@ -1061,26 +1129,28 @@ __device__ __forceinline__ void load_tiles(const KParams& p, SweepLds& L, const 
 // mask(r, j-1), shifted left by one with d(r, j) as its new lowest bit, so
 // that after the chunk's last column a step at column 32c + k sits at
 // position 31 - k.  Everything is complemented:
-//   v_lshrrev  b = wc >> 31        the lane's complemented decision;
-//   v_add_co   wc += wc            the same bit into VCC, wc moves on one bit;
+//   v_add_co   wc += wc            the lane's complemented decision into VCC;
+//   v_lshrrev  b' = wc >> 31       the next column's;
 //   v_cndmask_dpp  xc = VCC ? pc : pc of the lane below (wave_shr:1);
 //   v_lshl_or  pc = xc << 1 | b.
-// Only the last two depend on the previous column (the first two fill the
-// two wait states a DPP read needs after the VALU write of its source), and
-// neither writes VCC, so consecutive columns do not wait on each other's
+// Only the last two depend on the previous column (the others, with an s_nop,
+// fill the two wait states between a VALU write of VCC or of a DPP source and
+// its use), and // neither writes VCC, so consecutive columns do not wait on each other's
 // carry.  Lane 0 (the row above the wave) has no lane below: DPP leaves its
 // xc unwritten, all ones (mask 0), so a path that climbs into it contributes
 // nothing more.
 __device__ __forceinline__ void mask_cols8(uint32_t& wc, uint32_t& xc, uint32_t pc, uint32_t (&o)[8]) {
   uint32_t b0, b1;
-#define MAS_MASK_COL(P, O, B)                                                         \
-  "v_lshrrev_b32 %[" B "], 31, %[w]\n\t"                                              \
+#define MAS_MASK_COL(P, O, B, BN)                                                     \
   "v_add_co_u32 %[w], vcc, %[w], %[w]\n\t"                                            \
+  "v_lshrrev_b32 %[" BN "], 31, %[w]\n\t"                                             \
+  "s_nop 0\n\t"                                                                       \
   "v_cndmask_b32_dpp %[x], %[" P "], %[" P "], vcc wave_shr:1 row_mask:0xf bank_mask:0xf\n\t" \
   "v_lshl_or_b32 %[" O "], %[x], 1, %[" B "]\n\t"
-  asm volatile(MAS_MASK_COL("p", "o0", "b0") MAS_MASK_COL("o0", "o1", "b1") MAS_MASK_COL("o1", "o2", "b0")
-               MAS_MASK_COL("o2", "o3", "b1") MAS_MASK_COL("o3", "o4", "b0") MAS_MASK_COL("o4", "o5", "b1")
-               MAS_MASK_COL("o5", "o6", "b0") MAS_MASK_COL("o6", "o7", "b1")
+  asm volatile("v_lshrrev_b32 %[b0], 31, %[w]\n\t"
+               MAS_MASK_COL("p", "o0", "b0", "b1") MAS_MASK_COL("o0", "o1", "b1", "b0") MAS_MASK_COL("o1", "o2", "b0", "b1")
+               MAS_MASK_COL("o2", "o3", "b1", "b0") MAS_MASK_COL("o3", "o4", "b0", "b1") MAS_MASK_COL("o4", "o5", "b1", "b0")
+               MAS_MASK_COL("o5", "o6", "b0", "b1") MAS_MASK_COL("o6", "o7", "b1", "b0")
                : [o0] "=&v"(o[0]), [o1] "=&v"(o[1]), [o2] "=&v"(o[2]), [o3] "=&v"(o[3]), [o4] "=&v"(o[4]),
                  [o5] "=&v"(o[5]), [o6] "=&v"(o[6]), [o7] "=&v"(o[7]), [w] "+v"(wc), [x] "+v"(xc), [b0] "=&v"(b0),
                  [b1] "=&v"(b1)
@@ -1089,82 +1159,119 @@ __device__ __forceinline__ void mask_cols8(uint32_t& wc, uint32_t& xc, uint32_t 
 #undef MAS_MASK_COL
 }
 
-// A finisher wave: for every chunk of its sweep wave, once that wave's
-// decision words of the chunk are in the ring slot (its progress passes c+1),
-// reads them, frees the slot, computes the step masks of the wave's rows and
-// of its last row entered at every position, and stores them to
-// pm[b][c][kEntPerWave * g + ...] with device-scope write-through stores.
-// Decisions at columns >= t_y (the last chunk's tail) count as "stay", so
-// that the last row's mask describes the path from (t_x-1, t_y-1).  Once all
-// of its stores have landed, the wave's done flag goes up.  The work is kept
-// out of the sweep waves, whose column chain sets the pace, and out of the
-// loaders, whose waits count their own loads only.
-__device__ __forceinline__ void finisher_role(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
-  const int lane = x.lane, w = x.w;
-  if (x.g > x.g_last) return;
-  const int C = (x.ty + kChunk - 1) / kChunk;
-  const uint32_t top_keep = ~0u << (kChunk - 1 - (x.ty - 1) % kChunk);
+// The finisher waves: finisher f takes chunks c_begin + k, k = f - w mod 3, of
+// sweep waves w = 0 and 1.  For each, once the sweep wave's decision words are
+// in the ring slot, it reads them, frees the slot, computes the step masks of
+// the wave's rows and of its last row entered at every position, and stores
+// them to pm[b][c] with device-scope write-through stores.  Decisions at columns >= t_y (the last chunk's tail) count as
+// "stay", so that the last row's mask describes the path from (t_x-1,
+// t_y-1).  The finisher whose stores of a wave land last raises the wave's
+// done flag.  The work is kept out of the sweep waves, whose column chain
+// sets the pace, and out of the loaders, whose waits count their own loads
+// only.
+__device__ __forceinline__ void finish_chunk(const KParams& p, SweepLds& L, const WaveCtx& x, int c) {
+  const int lane = x.lane, w = x.w, slot = (c - x.c_begin) & (kRing - 1);
+  const uint32_t bits = *reinterpret_cast<const uint32_t*>(&L.u.ring[w][slot * kSlotStride + kBitsOff + 4 * lane]);
+  lgkm_wait0();
+  lds_put(lds_off(&L.box[w][kTaken + slot]), c + 1);  // the slot's words may be overwritten
   const __amdgpu_buffer_rsrc_t dr = make_cursor(p.pm + (size_t)x.b * p.NC * (size_t)p.EP, (uint64_t)p.NC * p.EP * 4u).rsrc();
   const __amdgpu_buffer_rsrc_t ddr = make_cursor(p.pd + (size_t)x.b * p.NC * (size_t)p.EP, (uint64_t)p.NC * p.EP).rsrc();
-  const int base = kEntPerWave * x.g;
-  const int row_off = lane > 0 ? 4 * (base + lane - 1) : -1;  // lane 0's mask (the row above) is not stored
-  const int mid_off = lane >= kWave - 8 ? 4 * (base + kMidOff + 4 * (lane - (kWave - 8))) : -1;
-  // Descent bytes: rows after every wave's mid entries (see mas_layout.h).
-  const int row_doff = lane > 0 ? pd_row0(p.NW) + kRowsPerWave * x.g + lane - 1 : -1;
-  const int mid_doff = lane >= kWave - 8 ? kChunk * x.g + 4 * (lane - (kWave - 8)) : -1;
-  const int q0 = 4 * (lane - (kWave - 8));  // the first mid entry a lane in 56..63 stores
-  const int* const progress = w > 0 ? reinterpret_cast<const int*>(&L.box[w - 1]) + 2 : &L.cons0;
-  const uint32_t taken_addr = lds_off(&L.box[w]) + 12u;
-  const uint32_t* const bits0 = reinterpret_cast<const uint32_t*>(&L.u.ring[w][kBitsOff]);
-  for (int c = x.c_begin; c < x.c_end && !bd.out; ++c) {
-    wait_at_least(progress, c + 2, bd);
-    const uint32_t bits = bits0[((c - x.c_begin) & (kRing - 1)) * (kSlotStride / 4) + lane];
-    lgkm_wait0();
-    lds_put(taken_addr, c + 1);  // the slot is free again
-    uint32_t wd = lane > 0 ? bits : 0u;
-    if (c == C - 1) wd &= top_keep;
-    uint32_t wc = ~wd, xc = ~0u;
-    uint32_t h[kChunk];  // complemented masks after each column of the chunk
-    {
-      uint32_t o[8];
-      mask_cols8(wc, xc, ~0u, o);
+  // Rows after every wave's mid entries (see mas_layout.h); lane 0's mask (the
+  // row above) is not stored.
+  const int q0 = 4 * (kWave - 1 - lane);  // the first mid entry a lane in 56..63 stores
+  const int row_doff = lane > 0 ? ent_row0(p.NW) + kRowsPerWave * x.g + lane - 1 : -1;
+  const int mid_doff = lane >= kWave - 8 ? kChunk * x.g + q0 : -1;
+  const int row_off = lane > 0 ? 4 * row_doff : -1, mid_off = lane >= kWave - 8 ? 4 * mid_doff : -1;
+  uint32_t wd = lane > 0 ? bits : 0u;
+  if (c == (x.ty - 1) / kChunk) wd &= ~0u << (kChunk - 1 - (x.ty - 1) % kChunk);
+  uint32_t wc = ~wd, xc = ~0u;
+  uint32_t h[kChunk];  // complemented masks after each column of the chunk
 #pragma unroll
-      for (int m = 0; m < 8; ++m) h[m] = o[m];
-      mask_cols8(wc, xc, h[7], o);
+  for (int k = 0; k < kChunk; k += 8) {
+    uint32_t o[8];
+    mask_cols8(wc, xc, k ? h[k - 1] : ~0u, o);
 #pragma unroll
-      for (int m = 0; m < 8; ++m) h[8 + m] = o[m];
-      mask_cols8(wc, xc, h[15], o);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) h[16 + m] = o[m];
-      mask_cols8(wc, xc, h[23], o);
-#pragma unroll
-      for (int m = 0; m < 8; ++m) h[24 + m] = o[m];
-    }
-    const int soff = c * p.EP * 4;
-    const uint32_t pm_row = ~h[kChunk - 1];
-    __builtin_amdgcn_raw_buffer_store_b32(pm_row, dr, row_off, soff, kPolicyDev);
-    {
-      // The row's descent byte (lane l: row l - 1 of the wave).
-      const int s_row = __builtin_popcount(pm_row);
-      const uint32_t d = s_row > lane - 1 ? kEscape + (31u - (uint32_t)__builtin_clz(pm_row | 1u)) : (uint32_t)s_row;
-      __builtin_amdgcn_raw_buffer_store_b8((uint8_t)d, ddr, row_doff, c * p.EP, kPolicyDev);
-    }
-    // Mid entry q: the last row's mask after column 31 - q, its positions
-    // raised by q; lane 63's values gathered into lanes 56..63, four each.
-    float hq[kChunk];
-#pragma unroll
-    for (int q = 0; q < kChunk; ++q) hq[q] = __uint_as_float(h[kChunk - 1 - q]);
-    const f32x4 f = gather_last_row(hq);
-    const u32x4 mv = {~__float_as_uint(f.x) << q0, ~__float_as_uint(f.y) << (q0 + 1), ~__float_as_uint(f.z) << (q0 + 2),
-                      ~__float_as_uint(f.w) << (q0 + 3)};
-    __builtin_amdgcn_raw_buffer_store_b128(mv, dr, mid_off, soff, kPolicyDev);
-    const uint32_t md = (uint32_t)__builtin_popcount(mv.x) | (uint32_t)__builtin_popcount(mv.y) << 8 |
-                        (uint32_t)__builtin_popcount(mv.z) << 16 | (uint32_t)__builtin_popcount(mv.w) << 24;
-    __builtin_amdgcn_raw_buffer_store_b32(md, ddr, mid_doff, c * p.EP, kPolicyDev);
+    for (int m = 0; m < 8; ++m) h[k + m] = o[m];
   }
-  vm_wait<0>();
-  if (lane == 0) st_dev(p.done + (size_t)x.b * p.NW + x.g, tag);
-  lds_put(lds_off(&L.fdone[w]), (int)tag);
+  const int soff = c * p.EP * 4;
+  const uint32_t pm_row = ~h[kChunk - 1];
+  __builtin_amdgcn_raw_buffer_store_b32(pm_row, dr, row_off, soff, kPolicyDev);
+  {
+    // The row's descent byte (lane l: row l - 1 of the wave).
+    const int s_row = __builtin_popcount(pm_row);
+    const uint32_t d = s_row > lane - 1 ? kEscape + (31u - (uint32_t)__builtin_clz(pm_row | 1u)) : (uint32_t)s_row;
+    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)d, ddr, row_doff, c * p.EP, kPolicyDev);
+  }
+  // Mid entry q: the last row's mask after column 31 - q, its positions
+  // raised by q; lane 63's values gathered into lanes 56..63, four each.
+  float hq[kChunk];
+#pragma unroll
+  for (int q = 0; q < kChunk; ++q) hq[q] = __uint_as_float(h[kChunk - 1 - q]);
+  f32x4 f;
+  gather_step<0>(f, hq);
+  gather_step<1>(f, hq + 4);
+  gather_step<2>(f, hq + 8);
+  gather_step<3>(f, hq + 12);
+  gather_step<4>(f, hq + 16);
+  gather_step<5>(f, hq + 20);
+  gather_step<6>(f, hq + 24);
+  gather_step<7>(f, hq + 28);
+  const u32x4 mv = {~__float_as_uint(f.x) << q0, ~__float_as_uint(f.y) << (q0 + 1), ~__float_as_uint(f.z) << (q0 + 2),
+                    ~__float_as_uint(f.w) << (q0 + 3)};
+  __builtin_amdgcn_raw_buffer_store_b128(mv, dr, mid_off, soff, kPolicyDev);
+  const uint32_t md = (uint32_t)__builtin_popcount(mv.x) | (uint32_t)__builtin_popcount(mv.y) << 8 |
+                      (uint32_t)__builtin_popcount(mv.z) << 16 | (uint32_t)__builtin_popcount(mv.w) << 24;
+  __builtin_amdgcn_raw_buffer_store_b32(md, ddr, mid_doff, c * p.EP, kPolicyDev);
+}
+
+__device__ __forceinline__ void finisher_role(const KParams& p, SweepLds& L, const WaveCtx& x0, const WaveCtx& x1, int f,
+                                              uint32_t tag, Bound& bd) {
+  if (x0.g > x0.g_last) return;
+  const int lane = x0.lane;
+  int c0 = x0.c_begin + f, c1 = x1.c_begin + (f + kFinishers - 1) % kFinishers;
+  const int e0 = x0.c_end, e1 = x1.g <= x1.g_last ? x1.c_end : 0;
+  // This finisher's part of wave w is in memory: the last of the finishers to
+  // get here raises the wave's flags.
+  auto finish = [&](int w, int g) __attribute__((always_inline)) {
+    vm_wait<0>();
+    int n = 0;
+    if (lane == 0) n = (int)__hip_atomic_fetch_add(&L.fcount[w], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    if (uni(n) == kFinishers - 1) {
+      if (lane == 0) st_dev(p.done + (size_t)x0.b * p.NW + g, tag);
+      lds_put(lds_off(&L.fdone[w]), (int)tag);
+    }
+  };
+  bool open0 = true, open1 = e1 > 0;
+  int spins = 0;
+  while ((open0 || open1) && !bd.out) {
+    bool idle = true;
+    if (open0) {
+      if (c0 >= e0) {
+        finish(0, x0.g);
+        open0 = false;
+      } else if (uni(lds_poll(&L.box[1][kWords])) > c0) {
+        finish_chunk(p, L, x0, c0);
+        c0 += kFinishers;
+        idle = false;
+      }
+    }
+    if (open1) {
+      if (c1 >= e1) {
+        finish(1, x1.g);
+        open1 = false;
+      } else if (uni(lds_poll(&L.box[2][kWords])) > c1) {
+        finish_chunk(p, L, x1, c1);
+        c1 += kFinishers;
+        idle = false;
+      }
+    }
+    if (idle) {
+      if (++spins > bd.limit) bd.expire();
+      __builtin_amdgcn_s_sleep(1);
+    } else {
+      spins = 0;
+    }
+  }
 }
 
 // ---------------------------------------------------------------- backtrack
@@ -1190,7 +1297,7 @@ __device__ __forceinline__ void load_windows(const KParams& p, SweepLds& L, int 
   const bool banded = wg.banded;
   const int nslot = wg.nslot;
   const int loads = wg.loads;
-  const int row0 = pd_row0(p.NW);
+  const int row0 = ent_row0(p.NW);
   const uint32_t slot_bytes = (uint32_t)wg.ent;
   const uint32_t win0 = lds_off(&L.u.walk.area[0]);
   const uint32_t ready_addr = lds_off(&L.wready) + 4u * (uint32_t)k;
@@ -1268,10 +1375,6 @@ __device__ __forceinline__ void load_windows(const KParams& p, SweepLds& L, int 
   t_rdy.flush(trace_of(p).win + ((size_t)b * kWinLoaders + k) * 2 * kWave + kWave);
 }
 
-// llvm.amdgcn.writelane (v_writelane_b32): lane l of `old` becomes v (v and l
-// wave-uniform), the other lanes keep theirs.
-extern "C" __device__ int mas_writelane(int v, int l, int old) __asm("llvm.amdgcn.writelane.i32");
-
 // Row starts from the walk's records of up to 64 chunks: lane k holds the
 // record of chunk base + k (valid when lo <= chunk <= hi): the step mask pm
 // of its path and the row e the path entered it in.  The k-th lowest set bit
@@ -1291,7 +1394,183 @@ __device__ __forceinline__ void flush_records(int* rsl, int base, int lo, int hi
   }
 }
 
-// The walker's helper, a finisher wave on another SIMD than the walker's:
+__device__ __forceinline__ void write_ones(const KParams& p, SweepLds& L, int b, int tx);
+__device__ __forceinline__ void publish_item(const KParams& p, int b, uint32_t tag, int lane);
+
+// Staging wave k of kStagers.  Flat modes: every kStagers-th KiB of the item's
+// step masks or descent bytes, all loads in flight at once.  Ring: blocks
+// qtop - k, qtop - k - kStagers, ... (descent bytes of chunks 4q .. 4q+3, in
+// slot q % blocks) once the walker has left the block that the slot held
+// (L.wpos: the block it walks).  A wave publishes in bready[k] that its blocks
+// >= bready[k] are there.  The walk's record starts as "not walked".
+constexpr int kStagers = 6;
+__device__ __forceinline__ int* walk_rows(SweepLds& L, const WalkPlan& wp) {
+  return reinterpret_cast<int*>(L.u.walk.area + (wp.mode == kRing4 ? wp.blocks * wp.bytes : wp.bytes));
+}
+__device__ __forceinline__ void stage_item(const KParams& p, SweepLds& L, int b, const WalkPlan& wp, int k, int lane, Bound& bd) {
+  const bool masks = wp.mode == kFlatMasks;
+  const size_t item = (size_t)b * p.NC * (size_t)p.EP;
+  const char* const src = masks ? reinterpret_cast<const char*>(p.pm + item) : reinterpret_cast<const char*>(p.pd + item);
+  const Cursor all = make_cursor(src, (uint64_t)p.NC * p.EP * (masks ? 4u : 1u));
+  const uint32_t dst = lds_off(&L.u.walk.area[0]);
+  if (k == 0) {
+    int* const rows = walk_rows(L, wp);
+    for (int c = lane; c < wp.chunks; c += kWave) rows[c] = -1;
+  }
+  if (wp.mode != kRing4) {
+    const __amdgpu_buffer_rsrc_t r = all.rsrc_s();
+    for (int o = 1024 * k; o < wp.bytes; o += 1024 * kStagers) dma16_dev(dst + (uint32_t)o, r, o + 16 * lane);
+    vm_wait<0>();
+    if (lane == 0) __hip_atomic_fetch_add(&L.staged, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    return;
+  }
+  const uint32_t ready_addr = lds_off(&L.bready[k]);
+  const int loads = wp.bytes / 1024;
+  int spins = 0;
+  lds_put(ready_addr, (wp.chunks - 1) / kBlk - k + 1);  // (none of its blocks lies above its first)
+  __builtin_amdgcn_s_setprio(3);
+  for (int q = (wp.chunks - 1) / kBlk - k; q >= 0; q -= kStagers) {
+    int at;
+    while ((at = uni(lds_poll(&L.wpos))) >= q + wp.blocks && !bd.out) {
+      if (++spins > bd.limit) bd.expire();
+      __builtin_amdgcn_s_sleep(1);
+    }
+    if (at < 0 || bd.out) break;
+    spins = 0;
+    Cursor c = all;
+    const int64_t off = (int64_t)q * kBlk * p.EP;
+    c.base += off;
+    c.left = (int)((int64_t)c.left - off);
+    const __amdgpu_buffer_rsrc_t r = c.rsrc_s();
+    const uint32_t to = dst + (uint32_t)((q % wp.blocks) * wp.bytes);
+    for (int n = 0; n < loads; ++n) dma16_dev(to + 1024u * (uint32_t)n, r, 1024 * n + 16 * lane);
+    vm_wait<0>();
+    lds_put(ready_addr, q - (kStagers - 1));
+  }
+  lds_put(ready_addr, -kNever);
+}
+
+// The walk of one item from (t_x-1, t_y-1) back to (0, 0) (Algorithm 1's
+// argmax loop, read off the step masks): per chunk, from the top, the mask's
+// population count or the descent byte of the row the path enters the chunk
+// in gives the row it leaves the chunk in: that many rows up, or, for a path
+// that climbs into the row above its wave at position p, to the wave's row
+// above and then as many rows as the mid entry p + 1 of the wave above says.
+// Leaves the row the path enters each chunk in walk_rows, for finish_item.
+//
+// A chunk's entry is one v_readlane of a register that holds the entries of
+// 64 consecutive rows of the chunk, read two chunks earlier from the row the
+// path enters the chunk above in (the path climbs at most 32 rows per chunk);
+// only a climb out of a wave (rare) reads LDS on the chain.  What bounds it is
+// that chain of dependent scalar instructions, one lone wave: the loop keeps
+// nothing but the chain, the record and the prefetch (rows lie in a row in
+// pm and pd, so its address is one subtraction).
+template <bool MASKS, bool RING>
+__device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const WalkPlan& wp, int tx, int lane, Bound& bd) {
+  using lds_u32 = __attribute__((address_space(3))) uint32_t;
+  using lds_u8 = __attribute__((address_space(3))) uint8_t;
+  constexpr int kEnt = MASKS ? 4 : 1;
+  const int area = (int)lds_off(&L.u.walk.area[0]), stride = p.EP * kEnt, row0 = ent_row0(p.NW) * kEnt;
+  int* const rows = walk_rows(L, wp);
+  // LDS address of chunk ch's first entry.
+  auto chunk_at = [&](int ch) __attribute__((always_inline)) -> int {
+    return RING ? area + (ch / kBlk % wp.blocks) * wp.bytes + ch % kBlk * stride : area + ch * stride;
+  };
+  // The entries of the chunk at LDS address `at` for rows eb, ..., eb - 63
+  // (lane k: row eb - k; lanes past row 0 read whatever is there).
+  const int lane_off = row0 - lane * kEnt;
+  auto fetch = [&](int at, int eb) __attribute__((always_inline)) -> uint32_t {
+    const uint32_t a = (uint32_t)(at + eb * kEnt + lane_off);
+    if (MASKS) return *(const lds_u32*)(uintptr_t)a;
+    return *(const lds_u8*)(uintptr_t)a;
+  };
+  // Ring: waits (bounded) until blocks >= q are staged.
+  auto ensure = [&](int q) __attribute__((always_inline)) {
+    int spins = 0;
+    while (!bd.out && __builtin_amdgcn_ballot_w64(*(volatile __attribute__((address_space(3))) int*)(uintptr_t)(lds_off(&L.bready[0]) + 4u * (uint32_t)min(lane, kStagers - 1)) > q) != 0) {
+      if (++spins > bd.limit) bd.expire();
+      __builtin_amdgcn_s_sleep(1);
+    }
+  };
+  int e = tx - 1, g = e / kRowsPerWave, cw = wp.chunks - 1;
+  int rr = e - kRowsPerWave * g;  // the row's place in its wave
+  int rec = -1;                   // lane k: the entry row of chunk (64-aligned base) + k
+  // One chunk: its entry from lane bp - e of P (P holds the chunk's entries
+  // from row bp down), then P refilled with those of the chunk at LDS address
+  // `next`, two chunks down, from the row the path enters the next chunk in.
+  auto body = [&](uint32_t& P, int& bp, int next) __attribute__((always_inline)) {
+    const uint32_t m = (uint32_t)__builtin_amdgcn_readlane((int)P, bp - e);
+    int up = MASKS ? __builtin_popcount(m) : (int)m;
+    if (__builtin_expect(MASKS ? up > rr : m >= kEscape, 0)) {
+      const int pos = MASKS ? 31 - __builtin_clz(m) : (int)(m - kEscape);
+      up = rr + 1;
+      if (pos < kChunk - 1) {
+        const uint32_t mid = (uint32_t)(chunk_at(cw) + (kChunk * (g - 1) + pos + 1) * kEnt);
+        if (MASKS)
+          up += __builtin_popcount((uint32_t)uni((int)*(const lds_u32*)(uintptr_t)mid));
+        else
+          up += uni((int)*(const lds_u8*)(uintptr_t)mid);
+      }
+      g -= 1;
+      rr += kRowsPerWave;
+    }
+    rec = mas_writelane(e, cw & (kWave - 1), rec);
+    e -= up;
+    rr -= up;
+    P = fetch(next, e);
+    bp = e;
+    cw -= 1;
+    // The next chunk's v_readlane stays after this prefetch: hoisted above
+    // it, it would wait for the prefetch it reads to be the last LDS load in
+    // flight rather than the last but one.
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // The record of the 64-aligned group whose lowest walked chunk is lo.
+  auto flush = [&](int lo) __attribute__((always_inline)) {
+    const int c = (lo & ~(kWave - 1)) + lane;
+    if (c >= lo && c < wp.chunks) rows[c] = rec;
+    lgkm_wait0();
+  };
+  if (e > 0) {
+    const int qtop = cw / kBlk;
+    if (RING)
+      ensure(max(qtop - 1, 0));
+    else
+      wait_at_least(&L.staged, kStagers, bd);
+    uint32_t Pa = fetch(chunk_at(cw), e), Pb = fetch(chunk_at(max(cw - 1, 0)), e);
+    int ba = e, bb = e;
+    lgkm_wait0();
+    // The chunks of the topmost, partial block one by one, then whole blocks.
+    while (cw >= 0 && (cw & (kBlk - 1)) != kBlk - 1) {
+      body(Pa, ba, chunk_at(max(cw - 2, 0)));
+      const uint32_t t = Pa;
+      Pa = Pb;
+      Pb = t;
+      const int tb = ba;
+      ba = bb;
+      bb = tb;
+      if (((cw + 1) & (kWave - 1)) == 0) flush(cw + 1);
+    }
+    while (cw >= 0 && e > 0) {
+      const int q = cw / kBlk;
+      if (RING) {
+        lds_put(lds_off(&L.wpos), q);
+        ensure(max(q - 1, 0));
+        lgkm_wait0();
+      }
+      const int here = chunk_at(kBlk * q), below = chunk_at(kBlk * max(q - 1, 0));
+      body(Pa, ba, here + stride);
+      body(Pb, bb, here);
+      body(Pa, ba, below + 3 * stride);
+      body(Pb, bb, below + 2 * stride);
+      if (((cw + 1) & (kWave - 1)) == 0) flush(cw + 1);
+    }
+    if (((cw + 1) & (kWave - 1)) != 0) flush(cw + 1);
+  }
+  lds_put(lds_off(&L.wpos), -1);
+}
+
+// The walker's helper (the receiver wave):
 // turns the walker's records into row starts as the walker hands them over,
 // every 64 chunks, so that the walk does not stop for it.  A record is the
 // row the path entered a chunk in and its descent byte there; the helper
@@ -1317,11 +1596,11 @@ __device__ __forceinline__ void walk_helper(const KParams& p, SweepLds& L, int b
     const int c = base + lane;
     uint32_t pm = 0;
     if (c >= lo && c <= hi && e >= 0) {
-      const int g = e / kRowsPerWave, rr = e - g * kRowsPerWave;
+      const int g = e / kRowsPerWave;
       const uint32_t* const chunk = pm_item + (size_t)c * p.EP;
-      pm = ld_dev(chunk + kEntPerWave * g + rr);
+      pm = ld_dev(chunk + ent_row0(p.NW) + e);
       const uint32_t pos = d - kEscape;
-      if (d >= kEscape && pos < kChunk - 1) pm |= ld_dev(chunk + kEntPerWave * (g - 1) + kMidOff + pos + 1);
+      if (d >= kEscape && pos < kChunk - 1) pm |= ld_dev(chunk + kChunk * (g - 1) + pos + 1);
     }
     flush_records(walk_rs(L, p.T), base, lo, hi, pm, e, lane);
     lgkm_wait0();
@@ -1330,17 +1609,16 @@ __device__ __forceinline__ void walk_helper(const KParams& p, SweepLds& L, int b
   }
 }
 
-// The walk of one item from (t_x-1, t_y-1) back to (0, 0) (Algorithm 1's
-// argmax loop, read off the descent bytes): per chunk, from the top, the
-// byte of the row the path enters the chunk in gives the row it leaves the
+// The same walk from windows, for items of more than about 4000 rows, whose
+// blocks of whole chunks do not fit LDS: per chunk, from the top, the byte of
+// the row the path enters the chunk in gives the row it leaves the
 // chunk in: that many rows up, or, for a path that climbs into the row above
 // its wave at position p, to the wave's row above and then as many rows as
 // the mid entry p + 1 of the wave above says.  Each chunk's entry row and
 // byte go into lane (chunk % 64) of two registers; every 64 chunks the
-// helper turns them into row starts (walk_helper).  Builds row_start in
-// walk_rs: the first column of every row, with rs[0] = 0 and
-// rs[t_x .. T] = t_y.  Runs on the sweep wave that holds row t_x-1; the
-// loaders of its workgroup stage the windows.
+// helper turns them into row starts in walk_rs (walk_helper).  Runs on the
+// sweep wave that holds row t_x-1; other waves of its workgroup stage the
+// windows.
 //
 // A chunk's byte is one v_readlane of a register that holds the bytes of 64
 // consecutive rows of the chunk, read from its window two chunks earlier,
@@ -1355,8 +1633,6 @@ __device__ __forceinline__ void walk_helper(const KParams& p, SweepLds& L, int b
 // group.  Once the path is in row 0 the rest of its group is walked
 // all the same: row 0's bytes are zero.
 __device__ __forceinline__ void walk(const KParams& p, SweepLds& L, int b, int tx, int ty, int lane, Bound& bd) {
-  stamp(trace_of(p).item + 8 * (size_t)b + 1);
-  int* rsl = walk_rs(L, p.T);
   Stamps wstamps;
   Waited waited;  // (debug build) ticks spent waiting for windows
   int e = tx - 1;                      // row of the path at the current chunk's last column
@@ -1526,9 +1802,63 @@ __device__ __forceinline__ void walk(const KParams& p, SweepLds& L, int b, int t
   waited.flush(trace_of(p).item + 8 * (size_t)b + 4);
   wave_lds_sync();
   lds_put(lds_off(&L.wpos), -1);
-  if (lane == 0) rsl[0] = 0;
-  for (int i = tx + lane; i <= p.T; i += kWave) rsl[i] = ty;
-  wave_lds_sync();
+}
+
+// The end of an item, by all waves of the walking workgroup once the walk is
+// over (a barrier precedes): the rest of the row_start table, the outputs
+// made from it, and the item's publication or its path's ones.
+__device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const WalkPlan& wp, int b, int tx, int ty, uint32_t tag) {
+  const int tid = (int)threadIdx.x;
+  int* const rsl = walk_rs(L, p.T);
+  if (wp.mode != kWindows) {
+    // One thread per chunk: the step mask of the path in it (from LDS, or from
+    // memory), completed by the wave above where the path climbs out of its
+    // wave; the k-th lowest set bit is where row e - k begins.
+    const int* const rows = walk_rows(L, wp);
+    const uint32_t* const pm_item = p.pm + (size_t)b * p.NC * (size_t)p.EP;
+    for (int c = tid; c < wp.chunks; c += kThreads) {
+      const int e = rows[c];
+      if (e < 0) continue;
+      const int g = e / kRowsPerWave, at = c * p.EP, row = at + ent_row0(p.NW) + e;
+      const uint32_t* const staged = reinterpret_cast<const uint32_t*>(L.u.walk.area);
+      uint32_t m = wp.mode == kFlatMasks ? staged[row] : ld_dev(pm_item + row);
+      if (__builtin_popcount(m) > e - kRowsPerWave * g) {
+        const int pos = 31 - __builtin_clz(m), mid = at + kChunk * (g - 1) + pos + 1;
+        if (g > 0 && pos < kChunk - 1) m |= wp.mode == kFlatMasks ? staged[mid] : ld_dev(pm_item + mid);
+      }
+      for (int r = e; m != 0u && r >= 1; --r, m &= m - 1u) rsl[r] = c * kChunk + (kChunk - 1) - __builtin_ctz(m);
+    }
+  }
+  if (tid == 0) rsl[0] = 0;
+  for (int i = tx + tid; i <= p.T; i += kThreads) rsl[i] = ty;
+  __syncthreads();
+  if (!p.early) {
+    int32_t* const rs_out = p.row_start + (size_t)b * ((size_t)p.T + 1);
+    for (int i = tid; i <= p.T; i += kThreads) st_dev(reinterpret_cast<uint32_t*>(rs_out + i), (uint32_t)rsl[i]);
+  }
+  if (p.durations) {
+    // Frames per text row (Sec. 2: what the duration predictor learns): the
+    // row's span of columns; 0 for rows past t_x.
+    int32_t* const d = p.durations + (size_t)b * (size_t)p.T;
+    for (int i = tid; i < p.T; i += kThreads) d[i] = rsl[i + 1] - rsl[i];
+  }
+  if (p.early) {
+    // (every zero of the item has landed: its finishers' flags went up after
+    // that, and the staging waves have waited for all of them)
+    write_ones(p, L, b, tx);
+  } else if (p.path) {
+    vm_wait<0>();
+    __syncthreads();
+    if (tid < kWave) publish_item(p, b, tag, tid);
+  }
+  if (tid < kWave) stamp(trace_of(p).item + 8 * (size_t)b + 3);
+  // The item's status, now that every wave whose work reaches its outputs has
+  // passed its last wait: timed out if any of them gave up, or if a path
+  // writer gave up before the publication became visible to it.
+  if (tid == 0 && p.status) {
+    const bool tmo = ld_dev(p.tmo + b) == tag || ld_dev(&p.hdr->path_fail) == tag;
+    p.status[b] = tmo ? kItemSyncTimeout : kItemOk;
+  }
 }
 
 // ---------------------------------------------------------------- path writer
@@ -1572,6 +1902,41 @@ __device__ __forceinline__ void write_path_rows(const KParams& p, int b, int r0,
   }
 }
 
+// Small batches (KParams::early): the workgroups write their own part of the
+// path, without path writers.  Part f of 3 of the zeros of workgroup r's rows
+// of item b, by a finisher wave before its first chunk: 16-byte stores, bytes
+// at the ends of the range.  (Device scope: the ones that the item's walker
+// writes later, perhaps on another XCD, must not be overtaken by a cached zero.)
+__device__ __forceinline__ void zero_rows(const KParams& p, int b, int r, int f, int lane) {
+  const int r0 = r * kWavesPerBlock * kRowsPerWave, r1 = min(r0 + kWavesPerBlock * kRowsPerWave, p.T);
+  uint8_t* const begin = p.path + ((size_t)b * p.T + r0) * (size_t)p.S;
+  const int n = (r1 - r0) * p.S;
+  const __amdgpu_buffer_rsrc_t rs = make_cursor(begin, (uint64_t)n).rsrc_s();
+  const int head = min((int)(-(uintptr_t)begin & 15), n), tail = (n - head) & 15;
+  if (f == 0) {
+    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, rs, lane < head ? lane : -1, 0, kPolicyDev);
+    __builtin_amdgcn_raw_buffer_store_b8((uint8_t)0, rs, lane < tail ? n - tail + lane : -1, 0, kPolicyDev);
+  }
+  const u32x4 zero = {0u, 0u, 0u, 0u};
+  for (int k = head + 1024 * f; k < n - tail; k += 1024 * kFinishers)
+    __builtin_amdgcn_raw_buffer_store_b128(zero, rs, k + 16 * lane < n - tail ? k + 16 * lane : -1, 0, kPolicyDev);
+}
+
+// The ones of item b's path, by every wave of the walking workgroup from the
+// row_start table in LDS, once every zero of the item has landed: few rows
+// take a wave each, many 16 lanes each.  (Bounds are clamped to
+// the row, as in write_path_rows.)
+__device__ __forceinline__ void write_ones(const KParams& p, SweepLds& L, int b, int tx) {
+  const int* const rsl = walk_rs(L, p.T);
+  uint8_t* const item_path = p.path + (size_t)b * (size_t)p.T * (size_t)p.S;
+  const int per = tx <= 64 ? kWave : 16;
+  const int k = (int)threadIdx.x % per;
+  for (int i = (int)threadIdx.x / per; i < tx; i += kThreads / per) {
+    const int lo = max(rsl[i], 0), hi = min(rsl[i + 1], p.S);
+    for (int j = lo + k; j < hi; j += per) item_path[(size_t)i * p.S + j] = 1;
+  }
+}
+
 // The item published k-th in this call (its entry in the completion order
 // carries the call's tag), or -1 once the bounded wait times out.  That wait
 // spans whole sweeps and walks, so its bound grows with the longest item
@@ -1607,7 +1972,6 @@ __device__ __forceinline__ int wait_published(const KParams& p, int k, uint32_t 
 // waiting workgroup puts one poll rather than twelve on the memory system
 // at a time, beside the sweeps still running.
 __device__ __forceinline__ void path_writer(const KParams& p, SweepLds& L, uint32_t tag, int wv, int lane, Bound& bd) {
-  constexpr int kWaves = kThreads / kWave;
   const int ntiles = p.B * p.ntile;
   int max_chunks = 0;
   for (int i = lane; i < p.B; i += kWave)
@@ -1666,56 +2030,50 @@ __device__ __forceinline__ void sweep_role(const KParams& p, SweepLds& L, const 
   const int lane = x.lane, b = x.b, g = x.g, w = x.w, g_last = x.g_last;
   if (g > g_last) return;  // no rows of the alignment here
   float score;
-  if (g == g_last) {
-    score = g == 0 ? sweep_wave<0, 0>(p, L, x, tag, bd) : sweep_wave<1, 0>(p, L, x, tag, bd);
-  } else if (w < kWavesPerBlock - 1) {
-    score = g == 0 ? sweep_wave<0, 1>(p, L, x, tag, bd) : sweep_wave<1, 1>(p, L, x, tag, bd);
-  } else {
-    score = sweep_wave<1, 2>(p, L, x, tag, bd);
-  }
+  if (g == g_last)
+    score = sweep_wave<0>(p, L, x, tag, bd);
+  else if (w < kWavesPerBlock - 1)
+    score = sweep_wave<1>(p, L, x, tag, bd);
+  else
+    score = sweep_wave<2>(p, L, x, tag, bd);
   if (g != g_last) return;
 
   // The walker.
   if (lane == (x.tx - 1) - g_last * kRowsPerWave + 1 && p.score) p.score[b] = score;
-  walk(p, L, b, x.tx, x.ty, lane, bd);
+  const WalkPlan wp = walk_plan(x.ty, p.EP, p.T);
+  stamp(trace_of(p).item + 8 * (size_t)b + 1);
+  if (wp.mode == kFlatMasks)
+    walk_item<true, false>(p, L, wp, x.tx, lane, bd);
+  else if (wp.mode == kFlatBytes)
+    walk_item<false, false>(p, L, wp, x.tx, lane, bd);
+  else if (wp.mode == kRing4)
+    walk_item<false, true>(p, L, wp, x.tx, lane, bd);
+  else
+    walk(p, L, b, x.tx, x.ty, lane, bd);
   stamp(trace_of(p).item + 8 * (size_t)b + 2);
-  int32_t* rs_out = p.row_start + (size_t)b * ((size_t)p.T + 1);
-  const int* const rsl = walk_rs(L, p.T);
-  for (int i = lane; i <= p.T; i += kWave) st_dev(reinterpret_cast<uint32_t*>(rs_out + i), (uint32_t)rsl[i]);
-  if (p.durations) {
-    // Frames per text row (Sec. 2: what the duration predictor learns): the
-    // row's span of columns; 0 for rows past t_x.
-    int32_t* d = p.durations + (size_t)b * (size_t)p.T;
-    for (int i = lane; i < p.T; i += kWave) d[i] = rsl[i + 1] - rsl[i];
-  }
-  publish_item(p, b, tag, lane);
-  stamp(trace_of(p).item + 8 * (size_t)b + 3);
-  // The item's status, once every wave whose work reaches its outputs has
-  // passed its last wait: timed out if any of them (or this walker) gave up,
-  // or if a path writer gave up before the publication became visible to it.
-  vm_wait<0>();
-  const bool tmo = bd.out || ld_dev(p.tmo + b) == tag || ld_dev(&p.hdr->path_fail) == tag;
-  if (lane == 0 && p.status) p.status[b] = tmo ? kItemSyncTimeout : kItemOk;
 }
 
-template <bool ALIGNED>
-__device__ __forceinline__ void loader_role(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
-  const int lane = x.lane, b = x.b, g = x.g, g_last = x.g_last;
-  if (g <= g_last) {
-    if (g > 0 && x.w == 0)
-      load_tiles<ALIGNED, true>(p, L, x, tag, bd);
-    else
-      load_tiles<ALIGNED, false>(p, L, x, tag, bd);
+// A wave of the walking workgroup whose own work is done, number k of
+// kStagers: brings the item's step masks or descent bytes to LDS for the walk,
+// once every wave of the item has published its step masks (the waves of
+// earlier workgroups through their done flags in memory, this workgroup's
+// through LDS: no memory round trip).  Windows take four of these waves, and
+// the last one as the walker's helper.
+__device__ __forceinline__ void staging_role(const KParams& p, SweepLds& L, const WaveCtx& x, int k, uint32_t tag, Bound& bd) {
+  const int lane = x.lane, b = x.b, g_last = x.g_last;
+  const WalkPlan wp = walk_plan(x.ty, p.EP, p.T);
+  if (wp.mode == kWindows && k >= kWinLoaders) {
+    if (k == kStagers - 1) walk_helper(p, L, b, lane, bd);
+    return;
   }
-  if (!walker_workgroup(x)) return;
-  // Decision windows for the walk, once every wave of the item has published
-  // its step masks: the waves of earlier workgroups through their done
-  // flags in memory, this workgroup's through LDS (no memory round trip).
   const int g_own = (g_last / kWavesPerBlock) * kWavesPerBlock;
   wait_flags(p.done + (size_t)b * p.NW, g_own, tag, lane, bd);
   wait_tags(L.fdone, g_last - g_own + 1, tag, bd);
-  if (x.w == 0) stamp(trace_of(p).item + 8 * (size_t)b + 0);
-  load_windows(p, L, b, x.tx, x.ty, x.w, lane, bd);
+  if (k == 0) stamp(trace_of(p).item + 8 * (size_t)b + 0);
+  if (wp.mode == kWindows)
+    load_windows(p, L, b, x.tx, x.ty, k, lane, bd);
+  else
+    stage_item(p, L, b, wp, k, lane, bd);
 }
 
 // Items with invalid lengths: an all-zero slab, zero row_start, score -inf.
@@ -1730,7 +2088,7 @@ __device__ __forceinline__ void invalid_item(const KParams& p, int b, int g, boo
     if (p.status) p.status[b] = st;
   }
   // The path writers write the all-zero slab from this table.
-  publish_item(p, b, tag, lane);
+  if (p.path && !p.early) publish_item(p, b, tag, lane);
 }
 
 // The last workgroup of the call to finish clears the call's counters and
@@ -1753,19 +2111,24 @@ __device__ __forceinline__ void finish_call(const KParams& p, uint32_t gen) {
 
 // Twelve waves per workgroup (four sweep waves, four loaders, four
 // finishers), one workgroup per CU.
-template <bool ALIGNED>
-__global__ void __launch_bounds__(kThreads, 1) mas_kernel(KParams p) {
+__global__ void __launch_bounds__(kThreads, 4) mas_kernel(KParams p) {
   __shared__ SweepLds L;
   if (threadIdx.x == 0) stamp(trace_of(p).wg + 2 * (size_t)blockIdx.x);
-  if (__hip_atomic_load(&p.hdr->magic, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != kWsMagic) {
+  // The four words every workgroup starts from, asked for together: one
+  // memory round trip instead of four in a row.
+  const int sid = blockIdx.x;
+  const int r = sid / p.B, b = sid - r * p.B;
+  const uint32_t magic = __hip_atomic_load(&p.hdr->magic, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t gen = __hip_atomic_load(&p.hdr->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int tx = __hip_atomic_load(p.t_x + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int ty = __hip_atomic_load(p.t_y + b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (magic != kWsMagic) {
     // Not an initialised workspace: report it and touch nothing else.
     if (blockIdx.x == 0 && p.status)
       for (int i = threadIdx.x; i < p.B; i += blockDim.x) p.status[i] = kItemBadWorkspace;
     return;
   }
-  const uint32_t gen = __hip_atomic_load(&p.hdr->gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   const uint32_t tag = call_tag(gen);
-  const int sid = blockIdx.x;
   if (sid >= p.B * p.NB) {
     // A path writer.
     Bound bd{p.spin_limit, false, &p.hdr->path_fail, tag};
@@ -1775,16 +2138,13 @@ __global__ void __launch_bounds__(kThreads, 1) mas_kernel(KParams p) {
     finish_call(p, gen);
     return;
   }
-  const int b = sid % p.B;
-  const int r = sid / p.B;
   const int lane = threadIdx.x & (kWave - 1);
-  const int wv = uni(threadIdx.x / kWave);
-  const int w = wv & (kWavesPerBlock - 1);
-  const bool is_finisher = wv >= 2 * kWavesPerBlock;
-  const bool is_loader = wv >= kWavesPerBlock && !is_finisher;
+  // (the workgroups that come second to their CUs have their sweep waves on
+  // the SIMDs of the first one's finishers)
+  const int wv = uni(threadIdx.x / kWave) ^ (sid >> 7 & 2);
+  // The sweep wave this wave works for (the first where it is both).
+  const int w = wv < kWavesPerBlock ? wv : wv >= kLoader0 && wv < kLoader0 + kLoaders ? wv - kLoader0 : 0;
   const int g = r * kWavesPerBlock + w;
-  const int tx = p.t_x[b];
-  const int ty = p.t_y[b];
   const int st = item_status(tx, ty, p.T, p.S);
   Bound bd{p.spin_limit, false, p.tmo + b, tag};
 
@@ -1792,37 +2152,61 @@ __global__ void __launch_bounds__(kThreads, 1) mas_kernel(KParams p) {
   if (threadIdx.x < kWavesPerBlock) {
     // Nothing loaded or delivered yet; every wave's progress is just below
     // its first chunk (it first reads the boundary row of chunk c_begin-1).
+    // The item's first wave waits for no boundary rows.
     const int gg = r * kWavesPerBlock + (int)threadIdx.x;
-    L.box[threadIdx.x] = i32x4{chunk_begin(gg), chunk_begin(gg) - 1, chunk_begin(gg + 1) - 1, chunk_begin(gg)};
+    L.box[threadIdx.x + 1][kWords] = chunk_begin(gg);
+    int* const box = L.box[threadIdx.x];
+    box[kReady] = chunk_begin(gg);
+    for (int k = 0; k < kRing; ++k) box[kTaken + k] = chunk_begin(gg) + k - (kRing - 1);
+    box[kProd] = gg == 0 ? kNever : chunk_begin(gg) - 1;
+    box[kNext] = chunk_begin(gg + 1) - 1;
   }
   if (threadIdx.x == 0) {
     L.cons0 = chunk_begin(r * kWavesPerBlock) - 1;
+    L.released = 0;
     L.wready = i32x4{1 << 30, 1 << 30, 1 << 30, 1 << 30};
-    // Walker not started: at chunk C (every window slot free), row t_x-1.
-    lds_store(&L.wpos, walk_pos((ty + kChunk - 1) / kChunk, max(tx - 1, 0)));
+    // Walker not started: at the topmost block; windows: at chunk C (every
+    // window slot free), row t_x-1.
+    lds_store(&L.wpos, st != kItemOk || walk_plan(ty, p.EP, p.T).mode != kWindows
+                           ? (ty - 1) / (kChunk * kBlk)
+                           : walk_pos((ty + kChunk - 1) / kChunk, max(tx - 1, 0)));
   }
   if (threadIdx.x < kWave) L.wbase[threadIdx.x] = (int)lds_off(&L.u.walk.area[0]);
-  if (threadIdx.x < kWavesPerBlock) L.fdone[threadIdx.x] = 0u;  // never a tag (tags are odd)
+  if (threadIdx.x < kWavesPerBlock) L.fdone[threadIdx.x] = L.fcount[threadIdx.x] = 0u;  // (0 is never a tag)
   if (threadIdx.x == 0) {
+    L.staged = 0;
+    for (int k = 0; k < 8; ++k) L.bready[k] = kNever;
     L.req_posted = 0;
     L.req_done = 0;
   }
   __syncthreads();
 
+  const int f = wv == kFinisher2 ? 2 : wv >= kFinisher0 && wv < kLoader0 ? wv - kFinisher0 : -1;  // finisher f
+  if (p.early && f >= 0) zero_rows(p, b, r, f, lane);
   if (st != kItemOk) {
-    invalid_item(p, b, g, is_loader || is_finisher, lane, st, tag);
+    invalid_item(p, b, g, wv != 0, lane, st, tag);
   } else {
     const WaveCtx x = make_ctx(b, g, w, lane, tx, ty);
-    if (is_finisher) {
-      finisher_role(p, L, x, tag, bd);
-      // (the finisher two SIMDs away from the walker helps it)
-      if (walker_workgroup(x) && w == (((x.g_last & (kWavesPerBlock - 1)) + 2) & (kWavesPerBlock - 1)))
-        walk_helper(p, L, x.b, lane, bd);
-    }
-    else if (is_loader)
-      loader_role<ALIGNED>(p, L, x, tag, bd);
-    else
+    const bool walks = walker_workgroup(x);
+    if (wv < kFinisher0) {
       sweep_role(p, L, x, tag, bd);
+    } else if (wv == kReceiver) {
+      if (g == 0)
+        start_item(p, L, b, lane);
+      else if (g <= x.g_last)
+        receive_rows(p, L, x, tag, bd);
+      if (walks) staging_role(p, L, x, 5, tag, bd);
+    } else if (wv >= kLoader0 && wv < kLoader0 + kLoaders) {
+      if (g <= x.g_last) load_tiles(p, L, x, bd);
+      if (walks) staging_role(p, L, x, w, tag, bd);
+    } else {
+      finisher_role(p, L, x, make_ctx(b, g + 1, 1, lane, tx, ty), f, tag, bd);
+      if (walks) staging_role(p, L, x, kLoaders + f, tag, bd);
+    }
+    if (walks) {
+      __syncthreads();
+      finish_item(p, L, walk_plan(ty, p.EP, p.T), b, tx, ty, tag);
+    }
   }
   if (bd.out) __hip_atomic_store(&p.hdr->error, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   stamp(trace_of(p).wg + 2 * (size_t)blockIdx.x + 1);  // (one wave's stamp: the last to get here wins)
@@ -1871,13 +2255,9 @@ __global__ void __launch_bounds__(256) mas_ws_init_kernel(uint4* __restrict__ p,
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_mas(const KParams& p, hipStream_t stream) {
-  const int writers = p.path ? min(p.B * p.ntile, kPathWorkgroups) : 0;
+  const int writers = p.path && !p.early ? min(p.B * p.ntile, kPathWorkgroups) : 0;
   const dim3 grid((unsigned)(p.B * p.NB + writers)), block(kThreads);
-  const bool aligned = (p.S % 4 == 0) && ((uintptr_t)p.value % 16 == 0);
-  if (aligned)
-    hipLaunchKernelGGL(mas_kernel<true>, grid, block, 0, stream, p);
-  else
-    hipLaunchKernelGGL(mas_kernel<false>, grid, block, 0, stream, p);
+  hipLaunchKernelGGL(mas_kernel, grid, block, 0, stream, p);
   return hipGetLastError();
 }
 

@@ -3,7 +3,7 @@
 // Rows of an item are processed by 64-lane waves.  Lane 0 of wave g carries
 // the row above the wave (row 63g-1, a copy handed down by the previous
 // wave; for g = 0 the virtual -inf row above row 0) and lanes 1..63 own
-// rows 63g .. 63g+62, one text row per lane.  Four such waves (252 rows)
+// rows 63g .. 63g+62, one text row per lane.  Two such waves (126 rows)
 // share a workgroup with the waves that feed them.  Speech columns are processed in chunks of 32, and every lane
 // packs its row's 32 forward decisions of a chunk into one 32-bit word.
 #pragma once
@@ -15,8 +15,7 @@ namespace mas {
 
 constexpr int kWave = 64;                    // lanes per wavefront (CDNA)
 constexpr int kRowsPerWave = kWave - 1;      // text rows a wave owns (lanes 1..63)
-constexpr int kWavesPerBlock = 4;            // one wave per SIMD of a CU
-constexpr int kThreadsPerBlock = kWave * kWavesPerBlock;
+constexpr int kWavesPerBlock = 2;            // sweep waves of a workgroup
 constexpr int kChunk = 32;                   // speech columns per decision word
 constexpr size_t kAlign = 256;
 constexpr int kMaxRows = 8192;               // largest T (the walker keeps row_start in LDS)
@@ -30,33 +29,29 @@ constexpr int kMaxRows = 8192;               // largest T (the walker keeps row_
 // Step mask of row i in chunk c: the set of positions p (column 32c + 31 - p)
 // at which the backtrack, entering the chunk in row i at its last column,
 // moves up one row while walking back to the chunk's first column; row i - k
-// begins at the column of the k-th lowest position.  A wave stores, per chunk,
-// kEntPerWave entries at pm[b][c][kEntPerWave * g + ...]:
-//   entry r (r < 63):           the mask of its row 63g + r, for the path
-//                               while it stays in the wave's rows; a path that
-//                               climbs into the row above the wave ends there,
-//                               with that step as its highest position p;
-//   entry kMidOff + q (q < 32): the mask of the wave's last row entered at
-//                               position q (column 32c + 31 - q), positions
-//                               >= q, which completes such a path of the next
-//                               wave at q = p + 1.
-// A path climbs at most 32 rows per chunk, so it crosses at most one wave
-// boundary in a chunk.
+// begins at the column of the k-th lowest position.  Per chunk, pm[b][c] holds
+// EP = kEntPerWave * NW entries:
+//   32g + q (q < 32):  mid entry q of wave g: the mask of the wave's last row
+//                      entered at position q (column 32c + 31 - q), positions
+//                      >= q, which completes a path of the next wave that
+//                      climbs out of it, at q = p + 1 (below);
+//   ent_row0 + i:      the mask of text row i, for the path while it stays in
+//                      the rows of i's wave; a path that climbs into the row
+//                      above the wave ends there, with that step as its
+//                      highest position p.
+// Rows lie in a row whatever waves they belong to, so that the walk reads 64
+// rows' entries with one subtraction per lane.  A path climbs at most 32 rows
+// per chunk, so it crosses at most one wave boundary in a chunk.
 constexpr int kEntPerWave = 96;
-constexpr int kMidOff = 64;
-// Descent bytes, the walk's own copy of the step masks at a quarter of
-// their size.  Per chunk, EP bytes: first one byte per mid entry of every
-// wave (wave g's mid entry q at kChunk * g + q), then one byte per text row
-// (row i at pd_row0(NW) + i), so that consecutive rows have consecutive
-// bytes whatever waves they belong to:
-//   row i (in wave g):  the number of rows the path climbs in the chunk while
-//                       it stays in the wave's rows (the mask's popcount), or
-//                       64 + p when it climbs into the row above the wave at
-//                       position p (the highest position of the mask);
-//   mid entry q:        the popcount of mid entry q's mask.
-// (EP = 96 NW covers the 32 NW mid bytes and the 63 NW row bytes.)
+// Descent bytes pd[b][c], the walk's own copy of the step masks at a quarter of
+// their size, entry by entry:
+//   row i:        the number of rows the path climbs in the chunk while it
+//                 stays in the wave's rows (the mask's popcount), or 64 + p
+//                 when it climbs into the row above the wave at position p
+//                 (the highest position of the mask);
+//   mid entry q:  the popcount of mid entry q's mask.
 constexpr uint32_t kEscape = 64;
-__host__ __device__ constexpr int pd_row0(int NW) { return kChunk * NW; }
+__host__ __device__ constexpr int ent_row0(int NW) { return kChunk * NW; }
 
 // Boundary hand-off between consecutive workgroups of an item: the last wave
 // g of a workgroup publishes Q[63g+62][j] (its last row) for every column j it
@@ -64,13 +59,25 @@ __host__ __device__ constexpr int pd_row0(int NW) { return kChunk * NW; }
 // workgroup hand on through LDS).  The tag identifies the call (see
 // WsHeader), so stale words from earlier calls are never mistaken for fresh
 // ones.
-// Dense path: written in tiles of kPathTileRows rows of one item, taken in
-// the order the items' row_start tables are published, by at most
-// kPathWorkgroups path-writer workgroups (three quarters of the MI355X's 256
-// CUs: enough to keep up, while the stores of all 256 slow the sweeps still
-// running more than they gain; timed on full batches of mixed lengths).
+// Dense path of large batches: written in tiles of kPathTileRows rows of one
+// item, taken in the order the items' row_start tables are published, by at
+// most kPathWorkgroups path-writer workgroups (enough to keep up; with more of
+// them the sweeps still running lose more than the path gains: B = 64,
+// T = 1024, S = 4096, three draws: 198 / 165 / 168 us with 96, 201 / 169 / 169
+// with 128, 209 / 193 / 185 with 256, 223 / 207 / 197 with 384; B = 32,
+// T = 2048, S = 8192: 560, 557, 573 and 579 us).
 constexpr int kPathTileRows = 32;
-constexpr int kPathWorkgroups = 192;
+constexpr int kPathWorkgroups = 128;
+constexpr uint64_t kShapeSlack = 192;  // (shapes are accepted up to this much below 2^31 boundary regions)
+
+// Batches of at most this many cells (B T S) get their path from the sweep
+// workgroups themselves, zeros first (KParams::early): their launches wait on
+// chains of dependent steps, not on HBM, so that the zeros cost nothing before
+// the sweeps and only the ones are left after the walks.  Measured, path
+// writers / early: 14.9 / 10.9 us (1 x 32 x 32), 47.5 / 41.7 (32 x 256 x 1024),
+// 80.6 / 69.4 (32 x 512 x 2048), 119 / 122 (64 x 252 x 4096, 64.5 M cells), 174
+// / 235 (64 x 1024 x 4096).
+constexpr uint64_t kEarlyMaxCells = (uint64_t)64 << 20;
 
 struct WsHeader {
   uint32_t gen;         // call generation; tag of a call = 2 * gen + 1
@@ -91,13 +98,14 @@ __host__ __device__ inline size_t round_up(size_t x, size_t a) { return (x + a -
 struct Layout {
   int32_t B, T, S;
   int32_t NW;      // waves per item = ceil(T / 63)
-  int32_t NB;      // workgroups per item = ceil(NW / 4)
+  int32_t NB;      // workgroups per item = ceil(NW / 2)
+  int32_t NS;      // boundary word regions per item = ceil(NW / 4), shared by two workgroups each
   int32_t NC;      // chunks per item = ceil(S / 32)
   int32_t EP;      // step-mask entries per chunk of an item = kEntPerWave * NW
   size_t off_done;   // uint32 [B][NW] sweep-finished flags (tag values)
   size_t off_tmo;    // uint32 [B] per-item timeout flags (tag values)
   size_t off_order;  // uint64 [B] items in the order their row_start tables were published: tag << 32 | item
-  size_t off_slots;  // uint64 [B][NB][NC*32] boundary hand-off words of each workgroup's last wave
+  size_t off_slots;  // uint64 [B][NS][NC*32] boundary hand-off words of each workgroup's last wave
   size_t off_pm;     // uint32 [B][NC][EP] step masks
   size_t off_rs;     // int32  [B][T+1] row_start table (mas_forward_ex)
   size_t off_pd;     // uint8  [B][NC][EP] descent bytes
@@ -112,10 +120,11 @@ __host__ inline bool make_layout(int32_t B, int32_t T, int32_t S, Layout* L) {
   L->S = S;
   L->NW = (T + kRowsPerWave - 1) / kRowsPerWave;
   L->NB = (L->NW + kWavesPerBlock - 1) / kWavesPerBlock;
+  L->NS = (L->NW + 3) / 4;
   L->NC = (S + kChunk - 1) / kChunk;
   L->EP = kEntPerWave * L->NW;
   // Overflow guard: every product below stays far under 2^62 when these hold.
-  if ((uint64_t)B * (uint64_t)L->NB + kPathWorkgroups > 0x7fffffffull) return false;  // grid size
+  if ((uint64_t)B * (uint64_t)L->NS + kShapeSlack > 0x7fffffffull) return false;
   if ((uint64_t)B * (uint64_t)T * (uint64_t)S > (1ull << 46)) return false;
   // One item's value slab is addressed with signed 32-bit byte offsets.
   if ((uint64_t)T * (uint64_t)S * 4u >= (1ull << 31)) return false;
@@ -127,7 +136,7 @@ __host__ inline bool make_layout(int32_t B, int32_t T, int32_t S, Layout* L) {
   L->off_order = off;
   off = round_up(off + (size_t)B * sizeof(uint64_t), kAlign);
   L->off_slots = off;
-  off = round_up(off + (size_t)B * L->NB * (size_t)L->NC * kChunk * sizeof(uint64_t), kAlign);
+  off = round_up(off + (size_t)B * L->NS * (size_t)L->NC * kChunk * sizeof(uint64_t), kAlign);
   L->off_pm = off;
   off = round_up(off + (size_t)B * L->NC * (size_t)L->EP * sizeof(uint32_t), kAlign);
   L->off_rs = off;

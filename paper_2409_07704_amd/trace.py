@@ -26,7 +26,8 @@ _PKG = os.path.dirname(os.path.abspath(__file__))
 TRACE_LIB_PATH = os.path.join(_PKG, "libmas_trace.so")
 TICK_US = 0.01  # s_memrealtime runs at 100 MHz
 
-ROWS_PER_WAVE, WAVES_PER_BLOCK, CHUNK, PATH_TILE_ROWS, PATH_WORKGROUPS = 63, 4, 32, 32, 192
+ROWS_PER_WAVE, WAVES_PER_BLOCK, CHUNK, PATH_TILE_ROWS, PATH_WORKGROUPS = 63, 2, 32, 32, 128
+EARLY_MAX_CELLS = 64 << 20  # batches up to this many cells have no path writers
 
 _lib = None
 
@@ -66,7 +67,7 @@ def run(value, t_x, t_y, with_path: bool = True, warmup: int = 5):
     """Stamps of one traced launch on the current device: (layout, int64 array)."""
     L = lib()
     B, T, S = value.shape
-    lay = layout(B, T, S, with_path)
+    lay = layout(B, T, S, with_path and B * T * S > EARLY_MAX_CELLS)
     buf = torch.zeros(lay["total"], dtype=torch.int64, device=value.device)
     n = L.mas_workspace_bytes(B, T, S)
     wbuf = torch.empty(n + 256, dtype=torch.uint8, device=value.device)
@@ -162,7 +163,7 @@ def summary(lay, st, t_x, t_y, with_path: bool = True, top: int = 3):
     items.sort(key=lambda r: -r["published_us"])
     out["items"] = items
     out["longest"] = items[:top]
-    if with_path:
+    if with_path and (tile > 0).any():
         te = tile[:, 1][tile[:, 1] > 0]
         ts = tile[:, 0][tile[:, 0] > 0]
         out["path_first_tile_us"] = float(_rel(ts.min(), t0)) if len(ts) else float("nan")

@@ -1,0 +1,67 @@
+"""The routes a call takes through the alignment kernel, each at the sizes where
+it begins and ends, bit for bit against the oracle: workgroups of 126 rows
+(one, two, more than the boundary regions hold apart), walks from whole step
+masks, whole descent bytes, blocks and banded windows, the path written by the
+sweep workgroups (small batches) and by path writers (large ones), with rows
+and pointers that are not 16-byte aligned."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # B, T, S, lengths: what it reaches
+    (3, 1, 37, [(1, 37), (1, 1), (0, 5)]),                       # one row; an empty item
+    (2, 126, 126, [(126, 126), (125, 126)]),                     # one full workgroup, forced diagonal
+    (3, 127, 211, [(127, 211), (126, 127), (64, 64)]),           # a second workgroup of one row
+    (2, 253, 1001, [(253, 1001), (252, 999)]),                   # three workgroups, whole step masks
+    (2, 300, 2503, [(300, 2503), (190, 2500)]),                  # whole descent bytes
+    (2, 505, 1999, [(505, 1999), (504, 1500)]),                  # workgroups that share a boundary region
+    (2, 1010, 4101, [(1010, 4101), (700, 3333)]),                # blocks of descent bytes
+    (1, 4300, 4400, [(4300, 4390)]),                             # banded windows
+    (16, 1010, 4160, None),                                      # more cells than the sweep workgroups write
+]
+
+
+@pytest.mark.parametrize("B,T,S,lengths", CASES)
+@pytest.mark.parametrize("shift", [0, 1])
+def test_routes(B, T, S, lengths, shift):
+    import paper_2409_07704_amd as mas
+
+    if lengths is None:
+        if shift:
+            pytest.skip("one alignment is enough for the large batch")
+        lengths = [(T - 61 * b, S - 37 * b) for b in range(B)]
+    tx, ty = (np.array(v, dtype=np.int32) for v in zip(*lengths))
+    value, tx, ty = synth.normal_batch(B, T, S, tx, ty, seed=B * T + S)
+    print(f"[gpu-case] routes B={B} T={T} S={S} shift={shift}", flush=True)
+    op, os_, ost = oracle.mas(value, tx, ty)
+    n = value.size
+    # value `shift` floats and the path `shift` bytes off their allocations
+    v = torch.empty(n + 4, dtype=torch.float32, device="cuda")[shift : shift + n].view(B, T, S)
+    v.copy_(torch.from_numpy(value))
+    raw = torch.full((n + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    path = raw[16 + shift : 16 + shift + n].view(B, T, S)
+    x, y = torch.from_numpy(tx).cuda(), torch.from_numpy(ty).cuda()
+    score = torch.full((B,), 3.0, device="cuda")
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    rs = torch.full((B, T + 1), -7, dtype=torch.int32, device="cuda")
+    dur = torch.full((B, T), -7, dtype=torch.int32, device="cuda")
+    ws = mas.Workspace(B, T, S)
+    for _ in range(2):
+        mas.mas_forward_ex(v, x, y, path, score, status, workspace=ws)
+        mas.mas_search(v, x, y, rs, workspace=ws, durations_out=dur)
+    torch.cuda.synchronize()
+    assert np.array_equal(status.cpu().numpy(), ost)
+    assert score.cpu().numpy().tobytes() == os_.tobytes()
+    assert np.array_equal(path.cpu().numpy(), op)
+    edge = raw.cpu().numpy()
+    assert (edge[: 16 + shift] == 0xA5).all() and (edge[16 + shift + n :] == 0xA5).all()
+    assert np.array_equal(dur.cpu().numpy(), op.sum(axis=2, dtype=np.int32))
+    assert np.array_equal(rs.cpu().numpy()[:, 1:] - rs.cpu().numpy()[:, :-1], dur.cpu().numpy())
