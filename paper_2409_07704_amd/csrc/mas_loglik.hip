@@ -45,17 +45,26 @@ constexpr int kMinExp = -113;                     // scale exponents stay in ran
 constexpr int kXcds = 8;                          // MI355X: workgroups go to its 8 XCDs round-robin
 constexpr int kUnitStartCost = 3;                 // a unit's start-up, in tiles, for the schedule
 constexpr int kMaxWaves = 16;
+constexpr int kPolicyStream = 2;                  // cache policy nt: streaming
+// Value tensors larger than this (the memory-side cache) are stored past the
+// caches.  Measured, cached / streaming: 64 x 1024 x 4096, D = 80, unit
+// variance 310 / 270 us, followed by mas_search 598 / 548; 32 x 512 x 2048 (134
+// MB) 37.6 / 36.3 us, but 97 / 102 with the search, which then finds the values
+// in the cache.
+constexpr uint64_t kStreamBytes = (uint64_t)256 << 20;
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef int i32x4 __attribute__((ext_vector_type(4)));
 
 template <int KS>
 struct LlLds {
   // B-fragments of two tiles: [tile % 2][k-step][n-block][hi, lo][slot],
   // slot = gb_slot(lane, k-step) for the lane that reads it.
   half8 gb[2][KS][2][2][64];
-  int col_e[2][kLlCols];  // exponent of the columns' scale, per tile buffer
-  float col_c[2][kLlCols];  // unit variance: -|z_j|^2 / 2 of the columns, per tile buffer
+  alignas(16) int col_e[2][kLlCols];  // exponent of the columns' scale, per tile buffer
+  alignas(16) float col_c[2][kLlCols];  // unit variance: -|z_j|^2 / 2 of the columns, per tile buffer
   int64_t wsum[kMaxWaves];        // schedule: per-wave sums of a block reduction or scan
   long long first, last;          // schedule: this workgroup's first and last tile, unit << 32 | tile
 };
@@ -244,6 +253,13 @@ __device__ __forceinline__ int64_t block_scan(int64_t x, Lds& L, int64_t* total)
   return before + x;
 }
 
+// One step of the product of text rows (f) and frames (g): the text rows are
+// its rows, or (WIDE) its columns.
+template <bool WIDE>
+__device__ __forceinline__ f32x4 mfma(half8 f, half8 g, f32x4 acc) {
+  return WIDE ? __builtin_amdgcn_mfma_f32_16x16x32_f16(g, f, acc, 0, 0, 0) : __builtin_amdgcn_mfma_f32_16x16x32_f16(f, g, acc, 0, 0, 0);
+}
+
 // KS = k-steps of 32 (the padded 2 * Dp channels); VEC: D % 8 == 0 and mu,
 // log_sigma and z 16-byte aligned (16-byte loads of 8 channels); NB =
 // builder waves (8 while the MFMA waves fit in 128 VGPRs, else 4).
@@ -257,11 +273,11 @@ __device__ __forceinline__ int64_t block_scan(int64_t x, Lds& L, int64_t* total)
 // waves 8.. load the frames and build the B-fragments.  Each kind of wave
 // issues only one kind of global memory operation (stores, or loads), so
 // no wave ever waits on the other kind.
-template <int KS, bool VEC, int NB, bool UNIT>
+template <int KS, bool VEC, int NB, bool UNIT, bool WIDE>
 __global__ void __launch_bounds__((kLlWaves + NB) * 64)
     mas_loglik_kernel(const float* __restrict__ mu, const float* __restrict__ log_sigma, const float* __restrict__ z,
                       const int32_t* __restrict__ t_x, const int32_t* __restrict__ t_y, float* __restrict__ value,
-                      int32_t B, int32_t T, int32_t S, int32_t D, int32_t Dp, int32_t nrb) {
+                      int32_t B, int32_t T, int32_t S, int32_t D, int32_t Dp, int32_t nrb, int32_t stream) {
   __shared__ LlLds<KS> L;
   constexpr int kThreads = (kLlWaves + NB) * 64;
   constexpr int FPW = kLlCols / NB;              // frames per builder wave
@@ -442,8 +458,9 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
     const int r0 = U.i0 + wave * 16;
     const int ilast = U.ilast, slack = U.slack, ty = U.ty;
     half8 ahi[KS], alo[KS];
-    float ra[4];
-    int re[4];
+    constexpr int kOwn = WIDE ? 1 : 4;  // text rows a lane's results fall in
+    float ra[kOwn];  // their constants and scale exponents
+    int re[kOwn];
     {
       // A-fragments of this wave's 16 rows: lane (m, q) holds row m and
       // channels k = 32 ks + 8 q + e of F.  Small contractions keep F in
@@ -481,12 +498,12 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
           split8(f, er, ahi[ks], alo[ks]);
         }
       }
-      // Row constants of the four rows this lane's results fall in (rows
-      // 4 q + r, held by lane 4 q + r).
+      // Row constants of the rows this lane's results fall in: its own row m
+      // (WIDE), or rows 4 q + r, held by lane 4 q + r.
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        ra[r] = __shfl(asum, 4 * q + r, 64);
-        re[r] = __shfl(er, 4 * q + r, 64);
+      for (int r = 0; r < kOwn; ++r) {
+        ra[r] = WIDE ? asum : __shfl(asum, 4 * q + r, 64);
+        re[r] = WIDE ? er : __shfl(er, 4 * q + r, 64);
       }
     }
     // The item's slab of value as a buffer: lanes with nothing to write
@@ -496,13 +513,14 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
     const int ilo_w = r0, ihi_w = min(r0 + 15, ilast);
     // Per result row: its index (rows past the item's last get one no
     // column can be within `slack` of) and its byte offset in the slab.
-    int rr[4], roffb[4];
+    int rr[kOwn], roffb[kOwn];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int ii = r0 + 4 * q + r;
+    for (int r = 0; r < kOwn; ++r) {
+      const int ii = r0 + (WIDE ? m : 4 * q + r);
       rr[r] = ii <= ilast ? ii : (1 << 30);
       roffb[r] = ii <= ilast ? ii * S * 4 : 0;
     }
+    const int roff8 = (r0 + (m & 7)) * S * 4;  // (used when all 16 rows are the item's)
     lds_barrier();  // tile 0 is built
     for (int t = 0; t < ntiles; ++t) {
       const int buf = t & 1;
@@ -510,11 +528,12 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
       // Does this wave's 16 x 32 block hold a band cell?
       if (ilo_w <= ihi_w && c + kLlCols - 1 >= ilo_w && c <= ihi_w + slack && c < ty) {
         f32x4 h0 = {0.f, 0.f, 0.f, 0.f}, h1 = h0, x0 = h0, x1 = h0;
-        // B-fragments read ahead of their MFMAs (two k-steps with eight
-        // builder waves' register budget to spare, else one); the
+        // Frame fragments read ahead of their MFMAs (two k-steps where the
+        // registers allow it, else one: with two, the 12 k-steps of D = 192
+        // spilled 59 registers, 159 us for 32 x 512 x 2048); the
         // scheduling barriers keep the compiler from sinking each read onto
         // its use.
-        constexpr int kAhead = NB == 8 ? 1 : 2;
+        constexpr int kAhead = KS <= 5 || KS > 7 ? 1 : 2;
         half8 bf[kAhead + 1][4];
         auto read_b = [&](int ks, half8 (&o)[4]) {
           const int sl = gb_slot(lane, ks);
@@ -531,39 +550,101 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
           if (ks + kAhead < KS) read_b(ks + kAhead, bf[(ks + kAhead) % (kAhead + 1)]);
           __builtin_amdgcn_sched_barrier(0);
           const half8(&cb)[4] = bf[ks % (kAhead + 1)];
-          x0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(alo[ks], cb[0], x0, 0, 0, 0);
-          x1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(alo[ks], cb[1], x1, 0, 0, 0);
-          h0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[ks], cb[0], h0, 0, 0, 0);
-          h1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[ks], cb[1], h1, 0, 0, 0);
-          x0 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[ks], cb[2], x0, 0, 0, 0);
-          x1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ahi[ks], cb[3], x1, 0, 0, 0);
+          x0 = mfma<WIDE>(alo[ks], cb[0], x0);
+          x1 = mfma<WIDE>(alo[ks], cb[1], x1);
+          h0 = mfma<WIDE>(ahi[ks], cb[0], h0);
+          h1 = mfma<WIDE>(ahi[ks], cb[1], h1);
+          x0 = mfma<WIDE>(ahi[ks], cb[2], x0);
+          x1 = mfma<WIDE>(ahi[ks], cb[3], x1);
           __builtin_amdgcn_sched_barrier(0);
         }
-        // Lane l holds column l % 16 of each n-block, rows 4 (l / 16) + r.
-        // A cell is in the band when 0 <= j - i <= slack and j < t_y; a
-        // block wholly inside the band stores without per-cell checks.
-        const int j0 = c + (lane & 15), j1 = j0 + 16;
-        const int ce0 = L.col_e[buf][lane & 15] - 2 * kScaleExp, ce1 = L.col_e[buf][16 + (lane & 15)] - 2 * kScaleExp;
-        const float cc0 = UNIT ? L.col_c[buf][lane & 15] : 0.f, cc1 = UNIT ? L.col_c[buf][16 + (lane & 15)] : 0.f;
-        const bool inside = r0 + 15 <= ilast && c >= r0 + 15 && c + kLlCols - 1 - r0 <= slack && c + kLlCols <= ty;
-        if (inside) {
+        if constexpr (WIDE) {
+          // WIDE: the frames are the product's rows, the text rows its columns: lane
+          // l holds text row l % 16 and frames 4 (l / 16) + r of each n-block,
+          // four neighbouring cells of a row.  Lanes l and l ^ 8 swap a piece so
+          // that a store covers eight rows' whole 128 bytes: the stores bound
+          // the unit-variance producer (64 x 1024 x 4096: 189 us without any;
+          // 345 with one cell per lane in four 64-byte pieces of rows, 403 with
+          // 16-byte pieces in sixteen of them, 310 this way, 270 streaming).  A cell is in the band when 0 <=
+          // j - i <= slack and j < t_y; a block wholly inside the band stores
+          // without per-cell checks.
+          u32x4 v[2];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float v0 = (ra[r] + cc0) + ldexpf(h0[r] + x0[r], re[r] + ce0);
-            const float v1 = (ra[r] + cc1) + ldexpf(h1[r] + x1[r], re[r] + ce1);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), vr, roffb[r] + j0 * 4, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), vr, roffb[r] + j1 * 4, 0, 0);
+          for (int nb = 0; nb < 2; ++nb) {
+            const f32x4 h = nb ? h1 : h0, x = nb ? x1 : x0;
+            const int n0 = 16 * nb + 4 * q;
+            const i32x4 ce = *reinterpret_cast<const i32x4*>(&L.col_e[buf][n0]);
+            f32x4 cc = {0.f, 0.f, 0.f, 0.f};
+            if (UNIT) cc = *reinterpret_cast<const f32x4*>(&L.col_c[buf][n0]);
+#pragma unroll
+            for (int r = 0; r < 4; ++r)
+              v[nb][r] = __float_as_uint((ra[0] + cc[r]) + ldexpf(h[r] + x[r], re[0] + (ce[r] - 2 * kScaleExp)));
+          }
+          const bool inside = r0 + 15 <= ilast && c >= r0 + 15 && c + kLlCols - 1 - r0 <= slack && c + kLlCols <= ty;
+          if (inside) {
+            // Store k: rows r0 + 8k .. r0 + 8k + 7; lanes l % 16 < 8 the first
+            // n-block's piece, the others the second's.
+            const bool low = m < 8;
+            u32x4 s0, s1;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const uint32_t give = low ? v[1][r] : v[0][r];
+              const uint32_t got = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)give, 0x128, 0xf, 0xf, false);  // row_ror 8
+              s0[r] = low ? v[0][r] : got;
+              s1[r] = low ? got : v[1][r];
+            }
+            const int jb = 4 * (c + 4 * q) + (low ? 0 : 64);
+            if (stream) {
+              __builtin_amdgcn_raw_buffer_store_b128(s0, vr, roff8 + jb, 0, kPolicyStream);
+              __builtin_amdgcn_raw_buffer_store_b128(s1, vr, roff8 + 32 * S + jb, 0, kPolicyStream);
+            } else {
+              __builtin_amdgcn_raw_buffer_store_b128(s0, vr, roff8 + jb, 0, 0);
+              __builtin_amdgcn_raw_buffer_store_b128(s1, vr, roff8 + 32 * S + jb, 0, 0);
+            }
+          } else {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb) {
+              // Whole pieces, then the cells of pieces that the band cuts.
+              const int j0 = c + 16 * nb + 4 * q;
+              bool in[4];
+#pragma unroll
+              for (int r = 0; r < 4; ++r) in[r] = j0 + r < ty && (unsigned)(j0 + r - rr[0]) <= (unsigned)slack;
+              const bool all = in[0] && in[1] && in[2] && in[3], cut = !all && (in[0] || in[1] || in[2] || in[3]);
+              __builtin_amdgcn_raw_buffer_store_b128(v[nb], vr, all ? roffb[0] + j0 * 4 : -1, 0, 0);
+              if (__builtin_amdgcn_ballot_w64(cut) != 0) {
+#pragma unroll
+                for (int r = 0; r < 4; ++r)
+                  __builtin_amdgcn_raw_buffer_store_b32(v[nb][r], vr, cut && in[r] ? roffb[0] + (j0 + r) * 4 : -1, 0, 0);
+              }
+            }
           }
         } else {
-          const bool c0 = j0 < ty, c1 = j1 < ty;
+          // Lane l holds column l % 16 of each n-block, rows 4 (l / 16) + r.
+          // A cell is in the band when 0 <= j - i <= slack and j < t_y; a
+          // block wholly inside the band stores without per-cell checks.
+          const int j0 = c + (lane & 15), j1 = j0 + 16;
+          const int ce0 = L.col_e[buf][lane & 15] - 2 * kScaleExp, ce1 = L.col_e[buf][16 + (lane & 15)] - 2 * kScaleExp;
+          const float cc0 = UNIT ? L.col_c[buf][lane & 15] : 0.f, cc1 = UNIT ? L.col_c[buf][16 + (lane & 15)] : 0.f;
+          const bool inside = r0 + 15 <= ilast && c >= r0 + 15 && c + kLlCols - 1 - r0 <= slack && c + kLlCols <= ty;
+          if (inside) {
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float v0 = (ra[r] + cc0) + ldexpf(h0[r] + x0[r], re[r] + ce0);
-            const float v1 = (ra[r] + cc1) + ldexpf(h1[r] + x1[r], re[r] + ce1);
-            const bool in0 = c0 && (unsigned)(j0 - rr[r]) <= (unsigned)slack;
-            const bool in1 = c1 && (unsigned)(j1 - rr[r]) <= (unsigned)slack;
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), vr, in0 ? roffb[r] + j0 * 4 : -1, 0, 0);
-            __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), vr, in1 ? roffb[r] + j1 * 4 : -1, 0, 0);
+            for (int r = 0; r < 4; ++r) {
+              const float v0 = (ra[r] + cc0) + ldexpf(h0[r] + x0[r], re[r] + ce0);
+              const float v1 = (ra[r] + cc1) + ldexpf(h1[r] + x1[r], re[r] + ce1);
+              __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), vr, roffb[r] + j0 * 4, 0, 0);
+              __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), vr, roffb[r] + j1 * 4, 0, 0);
+            }
+          } else {
+            const bool c0 = j0 < ty, c1 = j1 < ty;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float v0 = (ra[r] + cc0) + ldexpf(h0[r] + x0[r], re[r] + ce0);
+              const float v1 = (ra[r] + cc1) + ldexpf(h1[r] + x1[r], re[r] + ce1);
+              const bool in0 = c0 && (unsigned)(j0 - rr[r]) <= (unsigned)slack;
+              const bool in1 = c1 && (unsigned)(j1 - rr[r]) <= (unsigned)slack;
+              __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v0), vr, in0 ? roffb[r] + j0 * 4 : -1, 0, 0);
+              __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v1), vr, in1 ? roffb[r] + j1 * 4 : -1, 0, 0);
+            }
           }
         }
       }
@@ -572,19 +653,27 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
   }
 }
 
-template <int KS, bool UNIT>
+bool past_cache(int32_t B, int32_t T, int32_t S) { return (uint64_t)B * T * S * 4u > kStreamBytes; }
+
+// WIDE where it is the better one: for value tensors past the memory-side cache
+// (see kStreamBytes), and for more than 7 k-steps, whose results' row
+// constants would spill (32 x 512 x 2048, D = 192: 155 us, WIDE 120).  Smaller
+// tensors are written faster in the 64-byte pieces (32 x 512 x 2048, D = 80:
+// unit variance 35 us, WIDE 39; log-sigmas 45 and 47).
+template <int KS, bool UNIT, bool WIDE>
 hipError_t launch_ll_ks(const float* mu, const float* log_sigma, const float* z, const int32_t* t_x,
                         const int32_t* t_y, float* value, int32_t B, int32_t T, int32_t S, int32_t D, int32_t Dp,
                         bool vec, int grid, hipStream_t stream) {
   const int32_t nrb = (T + kLlRows - 1) / kLlRows;
+  const int32_t nt = past_cache(B, T, S);
   constexpr int NB = KS <= 5 ? 8 : 4;
   constexpr int kThreads = (kLlWaves + NB) * 64;
   if (vec)
-    hipLaunchKernelGGL((mas_loglik_kernel<KS, true, NB, UNIT>), dim3(grid), dim3(kThreads), 0, stream, mu, log_sigma, z,
-                       t_x, t_y, value, B, T, S, D, Dp, nrb);
+    hipLaunchKernelGGL((mas_loglik_kernel<KS, true, NB, UNIT, WIDE>), dim3(grid), dim3(kThreads), 0, stream, mu, log_sigma, z,
+                       t_x, t_y, value, B, T, S, D, Dp, nrb, nt);
   else
-    hipLaunchKernelGGL((mas_loglik_kernel<KS, false, NB, UNIT>), dim3(grid), dim3(kThreads), 0, stream, mu, log_sigma, z,
-                       t_x, t_y, value, B, T, S, D, Dp, nrb);
+    hipLaunchKernelGGL((mas_loglik_kernel<KS, false, NB, UNIT, WIDE>), dim3(grid), dim3(kThreads), 0, stream, mu, log_sigma, z,
+                       t_x, t_y, value, B, T, S, D, Dp, nrb, nt);
   return hipGetLastError();
 }
 
@@ -592,9 +681,17 @@ template <int KS>
 hipError_t dispatch_ll(int ks, const float* mu, const float* log_sigma, const float* z, const int32_t* t_x,
                        const int32_t* t_y, float* value, int32_t B, int32_t T, int32_t S, int32_t D, int32_t Dp,
                        bool vec, int grid, hipStream_t stream) {
-  if (ks == KS)
-    return log_sigma ? launch_ll_ks<KS, false>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream)
-                     : launch_ll_ks<KS, true>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream);
+  if (ks == KS) {
+    const bool wide = KS > 7 || past_cache(B, T, S);
+    if (log_sigma) {
+      if (wide) return launch_ll_ks<KS, false, true>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream);
+      if constexpr (KS <= 7)
+        return launch_ll_ks<KS, false, false>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream);
+    } else if constexpr (KS <= (kLoglikMaxD + 31) / 32) {  // (half the contraction without log_sigma)
+      return wide ? launch_ll_ks<KS, true, true>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream)
+                  : launch_ll_ks<KS, true, false>(mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream);
+    }
+  }
   if constexpr (KS > 1)
     return dispatch_ll<KS - 1>(ks, mu, log_sigma, z, t_x, t_y, value, B, T, S, D, Dp, vec, grid, stream);
   return hipErrorInvalidValue;
