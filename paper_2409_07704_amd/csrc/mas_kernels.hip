@@ -1600,7 +1600,7 @@ __device__ __forceinline__ void walk_helper(const KParams& p, SweepLds& L, int b
       const uint32_t* const chunk = pm_item + (size_t)c * p.EP;
       pm = ld_dev(chunk + ent_row0(p.NW) + e);
       const uint32_t pos = d - kEscape;
-      if (d >= kEscape && pos < kChunk - 1) pm |= ld_dev(chunk + kChunk * (g - 1) + pos + 1);
+      if (g > 0 && d >= kEscape && pos < kChunk - 1) pm |= ld_dev(chunk + kChunk * (g - 1) + pos + 1);
     }
     flush_records(walk_rs(L, p.T), base, lo, hi, pm, e, lane);
     lgkm_wait0();
@@ -1813,12 +1813,15 @@ __device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const
   if (wp.mode != kWindows) {
     // One thread per chunk: the step mask of the path in it (from LDS, or from
     // memory), completed by the wave above where the path climbs out of its
-    // wave; the k-th lowest set bit is where row e - k begins.
+    // wave; the k-th lowest set bit is where row e - k begins.  (The records lie
+    // where the value tiles were: when a wait was given up, a tile still in
+    // flight can have landed on them, so a record that is no row of the item is
+    // skipped, never used as an index.)
     const int* const rows = walk_rows(L, wp);
     const uint32_t* const pm_item = p.pm + (size_t)b * p.NC * (size_t)p.EP;
     for (int c = tid; c < wp.chunks; c += kThreads) {
       const int e = rows[c];
-      if (e < 0) continue;
+      if ((unsigned)e >= (unsigned)tx) continue;  // (-1: not walked)
       const int g = e / kRowsPerWave, at = c * p.EP, row = at + ent_row0(p.NW) + e;
       const uint32_t* const staged = reinterpret_cast<const uint32_t*>(L.u.walk.area);
       uint32_t m = wp.mode == kFlatMasks ? staged[row] : ld_dev(pm_item + row);

@@ -84,3 +84,31 @@ def test_tiny_wait_bound_reports_timeouts(mas, monkeypatch):
     _say("normal bound after a timed-out call")
     path, score, status = _call(mas, v, x, y, ws)
     assert np.array_equal(status, ost) and np.array_equal(path, op) and score.tobytes() == os_.tobytes()
+
+
+@pytest.mark.parametrize("B,T,S", [
+    (32, 512, 2048),  # walked from whole descent bytes
+    (3, 1010, 4101),  # ... from blocks of them
+    (1, 4300, 4400),  # ... from windows
+])
+def test_tiny_wait_bound_in_every_walk(mas, monkeypatch, B, T, S):
+    """The same for the walks whose records share LDS with tiles that may still
+    be landing when a wave gave up: the launch ends, an item reported OK is the
+    oracle's, and the next call with the normal bound is exact."""
+    tx = np.maximum(T - 17 * np.arange(B), 1).astype(np.int32)
+    ty = np.maximum(S - 31 * np.arange(B), tx).astype(np.int32)
+    value, tx, ty = synth.normal_batch(B, T, S, tx, ty, seed=T + S)
+    op, os_, ost = oracle.mas(value, tx, ty)
+    v, x, y = (torch.from_numpy(a).cuda() for a in (value, tx, ty))
+    ws = mas.Workspace(B, T, S)
+    _say(f"MAS_WAIT_BOUND=2 B={B} T={T} S={S}")
+    monkeypatch.setenv("MAS_WAIT_BOUND", "2")
+    path, score, status = _call(mas, v, x, y, ws)
+    monkeypatch.delenv("MAS_WAIT_BOUND")
+    assert set(np.unique(status).tolist()) <= {mas.ITEM_OK, mas.ITEM_SYNC_TIMEOUT}
+    assert (status == mas.ITEM_SYNC_TIMEOUT).any()
+    for b in np.flatnonzero(status == mas.ITEM_OK):
+        assert np.array_equal(path[b], op[b]) and score[b].tobytes() == os_[b].tobytes(), f"item {b} reported OK"
+    _say("normal bound after a timed-out call")
+    path, score, status = _call(mas, v, x, y, ws)
+    assert np.array_equal(status, ost) and np.array_equal(path, op) and score.tobytes() == os_.tobytes()
