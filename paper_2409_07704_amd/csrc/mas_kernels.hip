@@ -1852,7 +1852,14 @@ __device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const
   } else if (p.path) {
     vm_wait<0>();
     __syncthreads();
-    if (tid < kWave) publish_item(p, b, tag, tid);
+    if (tid < kWave) {
+      publish_item(p, b, tag, tid);
+      // The publication lands before this wave reads path_fail below; a writer
+      // that gives up stores path_fail, waits for it, then looks at the order
+      // again.  So one of the two sees the other: an item whose rows a writer
+      // left out never reports itself OK.
+      vm_wait<0>();
+    }
   }
   if (tid < kWave) stamp(trace_of(p).item + 8 * (size_t)b + 3);
   // The item's status, now that every wave whose work reaches its outputs has

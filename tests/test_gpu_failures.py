@@ -90,6 +90,7 @@ def test_tiny_wait_bound_reports_timeouts(mas, monkeypatch):
     (32, 512, 2048),  # walked from whole descent bytes
     (3, 1010, 4101),  # ... from blocks of them
     (1, 4300, 4400),  # ... from windows
+    (16, 1010, 4260),  # more cells than the sweep workgroups write: path writers give up too
 ])
 def test_tiny_wait_bound_in_every_walk(mas, monkeypatch, B, T, S):
     """The same for the walks whose records share LDS with tiles that may still
