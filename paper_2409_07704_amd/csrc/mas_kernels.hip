@@ -1852,20 +1852,20 @@ __device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const
   } else if (p.path) {
     vm_wait<0>();
     __syncthreads();
-    if (tid < kWave) {
-      publish_item(p, b, tag, tid);
-      // The publication lands before this wave reads path_fail below; a writer
-      // that gives up stores path_fail, waits for it, then looks at the order
-      // again.  So one of the two sees the other: an item whose rows a writer
-      // left out never reports itself OK.
-      vm_wait<0>();
-    }
+    if (tid < kWave) publish_item(p, b, tag, tid);
   }
   if (tid < kWave) stamp(trace_of(p).item + 8 * (size_t)b + 3);
   // The item's status, now that every wave whose work reaches its outputs has
   // passed its last wait: timed out if any of them gave up, or if a path
   // writer gave up before the publication became visible to it.
   if (tid == 0 && p.status) {
+    // The publication lands before path_fail is read; a writer that gives up
+    // stores path_fail, waits for it, then looks at the order again.  So one of
+    // the two sees the other: an item whose rows a writer left out never
+    // reports itself OK.  (Waited for here, not after publish_item, where it
+    // cost 220 more reads of spilled scalars over the kernel: 222 -> 226 us for
+    // 1 x 2048 x 8000.)
+    vm_wait<0>();
     const bool tmo = ld_dev(p.tmo + b) == tag || ld_dev(&p.hdr->path_fail) == tag;
     p.status[b] = tmo ? kItemSyncTimeout : kItemOk;
   }
