@@ -1056,15 +1056,25 @@ __device__ __forceinline__ void load_tiles(const KParams& p, SweepLds& L, const 
 // ---------------------------------------------------------------- receiver wave
 // The boundary rows of a workgroup's first sweep wave (of every workgroup but
 // an item's first).  The previous workgroup's last wave publishes Q of its
-// last row as {value, tag} words in global memory; the receiver polls four
-// chunks per device-scope load (lane l: the words of two columns), two loads
-// in flight, and moves the rows of the leading chunks whose 32 words all
-// carry this call's tag into their ring slots, as far as those are free, and
-// raises the sweep wave's prod, as a wave of the same workgroup would.  So
-// the sweep wave waits on LDS only.  (A wave of its own: a loader's polls
-// complete in order with its tile loads, and each cost a memory round trip of
-// the tiles: a workgroup ran 2.7 us behind the one above it, 0.06 us per
-// chunk slower.)  Words past the workgroup's region read as 0 (never a tag).
+// last row as {value, tag} words in global memory; the receiver polls them with
+// device-scope loads (lane l: the words of two columns), two loads in flight,
+// and moves the rows of the leading chunks whose 32 words all carry this
+// call's tag into their ring slots, as far as those are free, and raises the
+// sweep wave's prod, as a wave of the same workgroup would.  So the sweep wave
+// waits on LDS only.  (A wave of its own: a loader's polls complete in order
+// with its tile loads, and each cost a memory round trip of the tiles: a
+// workgroup ran 2.7 us behind the one above it, 0.06 us per chunk slower.)
+// A poll covers four chunks.  In large batches (KParams::stagger), which do
+// fill HBM, it covers two, and one chunk after a poll that delivered nothing:
+// most of their workgroups wait at any time, for a sweep above them that has
+// not started or is a chunk short, and what they ask for competes with the
+// value tiles.  Measured, four chunks / four, one after an empty poll / two,
+// one after an empty poll: 64 x 1024 x 4096 mixed lengths 173 / 164 / 162 us,
+// full lengths 319 / 308 / 298, 32 x 2048 x 8192 547 / 530 / 515; one chunk
+// always: 190, 312, 542.  A lone item of 17 workgroups, whose polls compete with
+// nothing, loses 0.5 % to the narrow ones (1 x 2048 x 8000).
+// (Chunks past the item's last are read, inside the workspace, but never
+// delivered, whatever their words hold.)
 __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
   const int lane = x.lane;
   const int band = x.g / kWavesPerBlock - 1;  // the workgroup above
@@ -1073,9 +1083,17 @@ __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, cons
   const uint32_t prod_addr = lds_off(&L.box[0][kProd]);
   const uint32_t ring = lds_off(&L.u.ring[0][0]) + kBoundOff + 8u * (uint32_t)(lane & 15);
   int next = x.c_begin - 1, cons = x.c_begin - 1, spins = 0;
+  // This lane's offset in a poll after one that delivered, and after one that
+  // did not (-1, past the resource: it loads nothing and gets 0, never a tag).
+  const int off_w = (lane < 32 || !p.stagger) ? 16 * lane : -1, off_n = (lane < 16 || !p.stagger) ? 16 * lane : -1;
+  int off = off_w;
   const int end = x.prev_end;
   auto poll = [&](int c0) __attribute__((always_inline)) -> u32x4 {
-    return __builtin_amdgcn_raw_buffer_load_b128(r, 16 * lane, c0 * (kChunk * 8), kPolicyDev);
+    const u32x4 wd = __builtin_amdgcn_raw_buffer_load_b128(r, off, c0 * (kChunk * 8), kPolicyDev);
+    // (keeps the offset out of the load's result registers: reused there, the
+    // next offset waited for both loads in flight)
+    asm volatile("" ::"v"(off));
+    return wd;
   };
   // Delivers what a poll from chunk c0 on holds past `next`.
   auto deliver = [&](int c0, u32x4 wd) __attribute__((always_inline)) {
@@ -1104,7 +1122,9 @@ __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, cons
       next = to;
       lds_put(prod_addr, next < end ? next : kNever);
       spins = 0;
+      off = off_w;
     } else {
+      off = off_n;
       if (++spins > bd.limit) bd.expire();
       __builtin_amdgcn_s_sleep(1);
     }
