@@ -66,6 +66,31 @@ static hipError_t prepare_workspace(void* ws, const Layout& L, hipStream_t strea
   return hipSuccess;
 }
 
+// Sweep workgroups of one launch, at most.  With 512 threads each, and the path
+// writers, far below 2^32 threads.
+constexpr int32_t kMaxGrid = 1 << 22;
+
+// The parameters of a launch for the n items from b0 on.
+static KParams items(KParams p, int32_t b0, int32_t n) {
+  const size_t b = (size_t)b0, T = (size_t)p.T, S = (size_t)p.S, ent = (size_t)p.NC * (size_t)p.EP;
+  p.B = n;
+  p.value += b * T * S;
+  p.t_x += b;
+  p.t_y += b;
+  p.row_start += b * (T + 1);
+  if (p.score) p.score += b;
+  if (p.status) p.status += b;
+  if (p.durations) p.durations += b * T;
+  if (p.path) p.path += b * T * S;
+  p.done += b * p.NW;
+  p.tmo += b;
+  p.order += b;
+  p.slots += b * p.NS * ((size_t)p.NC * kChunk);
+  p.pm += b * ent;
+  p.pd += b * ent;
+  return p;
+}
+
 static mas_status run(const float* value, const int32_t* t_x, const int32_t* t_y, const Layout& L,
                       int32_t* row_start, int32_t* durations, float* score, int32_t* status, uint8_t* path, void* ws,
                       hipStream_t stream, float sentinel = -INFINITY) {
@@ -103,7 +128,15 @@ static mas_status run(const float* value, const int32_t* t_x, const int32_t* t_y
   p.spin_limit = wait_bound();
   p.neg = sentinel;
   p.legacy = std::isfinite(sentinel) ? 1 : 0;
-  return launch_mas(p, stream) == hipSuccess ? MAS_OK : MAS_ERR_HIP;
+  // A grid holds less than 2^32 threads (a larger one loses workgroups without
+  // an error): batches of more items go in several launches on the stream, each
+  // with its part of every buffer.
+  const int32_t per = kMaxGrid / L.NB;
+  for (int32_t b0 = 0; b0 < L.B; b0 += per) {
+    if (launch_mas(items(p, b0, L.B - b0 < per ? L.B - b0 : per), stream) != hipSuccess) return MAS_ERR_HIP;
+    if (L.B - b0 <= per) break;  // (b0 + per may pass 2^31)
+  }
+  return MAS_OK;
 }
 
 // Workspace of mas_forward_static: one array per device, held until the

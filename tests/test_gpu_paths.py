@@ -65,3 +65,35 @@ def test_routes(B, T, S, lengths, shift):
     assert (edge[: 16 + shift] == 0xA5).all() and (edge[16 + shift + n :] == 0xA5).all()
     assert np.array_equal(dur.cpu().numpy(), op.sum(axis=2, dtype=np.int32))
     assert np.array_equal(rs.cpu().numpy()[:, 1:] - rs.cpu().numpy()[:, :-1], dur.cpu().numpy())
+
+
+def test_more_workgroups_than_a_grid_holds():
+    """4.3 M items of 127 padded rows: two workgroups each, more threads than one
+    launch can have.  One-token items have closed-form results."""
+    import paper_2409_07704_amd as mas
+
+    B, T, S = 4_300_000, 127, 1
+    print(f"[gpu-case] large grid B={B} T={T} S={S}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    value = torch.randn((B, T, S), generator=gen, device="cuda")
+    x = torch.ones(B, dtype=torch.int32, device="cuda")
+    y = torch.ones_like(x)
+    x[::1000] = 2  # infeasible
+    y[1::1000] = 0  # empty
+    ok = (x == 1) & (y == 1)
+    want = torch.where(y == 0, 1, torch.where(x == 2, 2, 0)).to(torch.int32)
+    score = torch.full((B,), 3.0, device="cuda")
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    ws = mas.Workspace(B, T, S)
+    for _ in range(2):
+        rs = torch.full((B, T + 1), -7, dtype=torch.int32, device="cuda")
+        mas.mas_search(value, x, y, rs, score, status, workspace=ws)
+        assert torch.equal(status, want)
+        assert torch.equal(score, torch.where(ok, value[:, 0, 0], -torch.inf))
+        assert (rs[:, 0] == 0).all() and (rs[:, 1:] == ok[:, None].to(torch.int32)).all()
+    del rs
+    path = torch.full((B, T, S), 0xA5, dtype=torch.uint8, device="cuda")
+    status.fill_(-1)
+    mas.mas_forward_ex(value, x, y, path, score, status, workspace=ws)
+    assert torch.equal(status, want)
+    assert torch.equal(path[:, 0, 0].bool(), ok) and not path[:, 1:].any()
