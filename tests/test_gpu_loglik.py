@@ -185,3 +185,44 @@ def test_benchmark_size(mas, ls_scale):
     check_values(mu, ls, z, value, tx, ty, cells=cells[np.sort(pick)], label=synth.BENCH_WORKLOAD)
     del cells, band
     check_alignment(mas, v, dx, dy, tx, ty, synth.BENCH_WORKLOAD)
+
+
+@pytest.mark.parametrize("ls_scale", [None, 0.2])
+def test_stores_past_the_cache_unaligned(mas, ls_scale):
+    """A value tensor just over 256 MB whose rows are not 16-byte aligned (S =
+    4099, and value_out one float off its allocation): whole pieces go by
+    16-byte streaming stores, pieces that the band cuts cell by cell.  Sampled
+    cells, those at both edges of the band among them, against the oracle, and
+    every cell outside the band untouched."""
+    B, T, S, D = 16, 1030, 4099, 80
+    assert B * T * S * 4 > 256 << 20
+    rng = np.random.default_rng(11)
+    tx = rng.integers(1, T + 1, B).astype(np.int32)
+    ty = np.array([int(rng.integers(a, S + 1)) for a in tx], np.int32)
+    tx[0], ty[0] = T, S
+    tx[1], ty[1] = 1000, 1000  # forced diagonal
+    tx[2], ty[2] = 1, S
+    tx[3] = 0
+    mu = rng.standard_normal((B, T, D)).astype(np.float32)
+    z = rng.standard_normal((B, S, D)).astype(np.float32)
+    ls = None if ls_scale is None else (ls_scale * rng.standard_normal((B, T, D))).astype(np.float32)
+    _say(f"B={B} T={T} S={S} D={D} log_sigma_scale={ls_scale} value_out off by one float")
+    n = B * T * S
+    raw = torch.full((n + 4,), float("nan"), dtype=torch.float32, device="cuda")
+    v = raw[1 : 1 + n].view(B, T, S)
+    assert v.data_ptr() % 16 != 0
+    dev = [None if a is None else torch.from_numpy(a).cuda() for a in (mu, ls, z, tx, ty)]
+    mas.mas_loglik(*dev, v)
+    torch.cuda.synchronize()
+    assert torch.isnan(raw[:1]).all() and torch.isnan(raw[1 + n :]).all()
+    value = v.cpu().numpy()
+    band = band_mask(tx, ty, T, S)
+    assert np.isnan(value[~band]).all() and not np.isnan(value[band]).any()
+    edge = []
+    for b in range(B):
+        i = np.arange(tx[b])
+        for j in (i, i + ty[b] - tx[b]):
+            edge.append(np.stack([np.full_like(i, b), i, j], 1))
+    cells = np.argwhere(band)
+    cells = np.concatenate([cells[rng.choice(len(cells), 100_000, replace=False)], *edge])
+    check_values(mu, ls, z, value, tx, ty, cells=cells, label="past the cache, unaligned")

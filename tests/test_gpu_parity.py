@@ -175,9 +175,8 @@ def test_full_length_batch(mas):
 
 
 def test_long_items(mas):
-    """Long speech axes: a backtrack over hundreds of chunks with banded
-    decision windows (T above the window height), a path pinned to the last
-    diagonal by a ridge of high values, and lengths around 1024 chunks with
+    """Long speech axes: a backtrack over hundreds of chunks from blocks of
+    descent bytes (T = 1500), a path pinned to the last diagonal by a ridge of high values, and lengths around 1024 chunks with
     the walking wave last in its workgroup (t_x 190 and 252)."""
     st = synth.Stream(91)
     B, T, S = 3, 1500, 9000
@@ -202,8 +201,8 @@ def test_long_items(mas):
 
 
 def test_banded_walk_windows(mas):
-    """Items taller than the walk's whole-chunk windows allow (t_x above
-    about 4350 rows at these shapes): the loaders stage banded windows, a
+    """Items taller than three blocks of whole chunks in LDS allow (T above
+    3024 rows at these lengths): four waves stage banded windows, a
     row band around the walker plus the mid entries of its waves, and the
     walk crosses many wave boundaries through them.  T = 8192 is the largest
     height the library accepts."""
@@ -217,10 +216,10 @@ def test_banded_walk_windows(mas):
 
 
 def test_mixed_batch_tall_items(mas):
-    """A mixed batch with T above the walk's window height (banded windows),
-    several workgroups per item (boundary rows handed on by the loaders, one
-    storer per workgroup) and many path tiles per item, plus degenerate items
-    (single row, diagonal, empty) in the same launch."""
+    """A mixed batch of tall items: many workgroups per item (boundary rows
+    handed on through memory to the next one's receiver), walks from blocks of
+    descent bytes, many path tiles per item, plus degenerate items (single row,
+    diagonal, empty) in the same launch."""
     st = synth.Stream(123)
     B, T, S = 12, 2048, 3000
     value = st.normal_f32(B * T * S).reshape(B, T, S) * np.float32(3.0) - np.float32(1.0)
@@ -230,7 +229,7 @@ def test_mixed_batch_tall_items(mas):
     tx[1], ty[1] = 1500, 1500    # diagonal
     tx[2], ty[2] = 1, 2999       # one row
     tx[3], ty[3] = 0, 100        # empty
-    tx[4], ty[4] = 1100, 2999    # just above the window height
+    tx[4], ty[4] = 1100, 2999    # nine workgroups
     assert_parity(mas, value, tx, ty, "mixed-tall-b12-t2048-s3000")
 
 

@@ -1,7 +1,7 @@
 """The routes a call takes through the alignment kernel, each at the sizes where
 it begins and ends, bit for bit against the oracle: workgroups of 126 rows
 (one, two, more than the boundary regions hold apart), walks from whole step
-masks, whole descent bytes, blocks and banded windows, the path written by the
+masks, whole descent bytes, blocks, banded windows and windows of whole chunks, the path written by the
 sweep workgroups (small batches) and by path writers (large ones), with rows
 and pointers that are not 16-byte aligned."""
 from __future__ import annotations
@@ -24,7 +24,11 @@ CASES = [
     (2, 300, 2503, [(300, 2503), (190, 2500)]),                  # whole descent bytes
     (2, 505, 1999, [(505, 1999), (504, 1500)]),                  # workgroups that share a boundary region
     (2, 1010, 4101, [(1010, 4101), (700, 3333)]),                # blocks of descent bytes
+    (1, 2400, 6000, [(2400, 6000)]),                             # ... three blocks of four chunks in LDS
+    (2, 3024, 3500, [(3024, 3500), (2900, 3400)]),               # ... the tallest item three blocks hold
+    (1, 3025, 3500, [(3025, 3499)]),                             # banded windows from one row more on
     (1, 4300, 4400, [(4300, 4390)]),                             # banded windows
+    (1, 2, 530_000, [(2, 530_000)]),                             # few rows, a record past LDS: windows of whole chunks
     (16, 1010, 4160, None),                                      # more cells than the sweep workgroups write
 ]
 

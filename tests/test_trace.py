@@ -44,7 +44,7 @@ def fake_launch():
 def test_layout_offsets():
     lay = trace.layout(1, 126, 2048, with_path=True)
     assert (lay["NW"], lay["NB"], lay["NC"], lay["ntile"]) == (2, 1, 64, 4)
-    assert lay["grid"] == 1 + 4  # one sweep workgroup, min(B * ntile, 192) path writers
+    assert lay["grid"] == 1 + 4  # one sweep workgroup, min(B * ntile, 128) path writers
     assert lay["chunk"] == 2 * lay["grid"]
     assert lay["walk"] == lay["chunk"] + 1 * 2 * 64
     assert lay["total"] == lay["win"] + 1 * 4 * 2 * 64
