@@ -289,11 +289,12 @@ __device__ __forceinline__ WalkPlan walk_plan(int ty, int EP, int T) {
   }
   return w;
 }
-// Walker position: (chunk << 16) | row (chunk < 2048, row < 8192), or -1
-// once the walk is over.
-__device__ __forceinline__ int walk_pos(int chunk, int row) { return (chunk << 16) | row; }
-__device__ __forceinline__ int pos_chunk(int wp) { return wp >> 16; }
-__device__ __forceinline__ int pos_row(int wp) { return wp & 0xFFFF; }
+// Walker position: (chunk << 13) | row (chunk < 2^18, row < kMaxRows = 8192), or
+// -1 once the walk is over.
+__device__ __forceinline__ int walk_pos(int chunk, int row) { return (chunk << 13) | row; }
+__device__ __forceinline__ int pos_chunk(int wp) { return wp >> 13; }
+__device__ __forceinline__ int pos_row(int wp) { return wp & (kMaxRows - 1); }
+static_assert(kMaxRows <= 1 << 13, "a row fits its field");
 
 struct SweepLds {
   union {

@@ -29,6 +29,7 @@ CASES = [
     (1, 3025, 3500, [(3025, 3499)]),                             # banded windows from one row more on
     (1, 4300, 4400, [(4300, 4390)]),                             # banded windows
     (1, 2, 530_000, [(2, 530_000)]),                             # few rows, a record past LDS: windows of whole chunks
+    (1, 2, 1_100_000, [(2, 1_100_000)]),                         # ... with more than 2^15 chunks
     (16, 1010, 4160, None),                                      # more cells than the sweep workgroups write
 ]
 
