@@ -97,8 +97,8 @@ typedef enum mas_status {
 
 /*
  * Bytes of device workspace that mas_search / mas_forward_ex need for a
- * batch of this shape (decision bits, row hand-off slots, progress flags
- * and, for mas_forward_ex, the row_start table).  Returns 0 for invalid
+ * batch of this shape (step masks, row hand-off slots, progress flags and a
+ * row_start table for mas_forward_ex).  Returns 0 for invalid
  * shapes.  The workspace must be 256-byte aligned.
  */
 size_t mas_workspace_bytes(int32_t B, int32_t T, int32_t S);
@@ -194,8 +194,9 @@ mas_status mas_loglik(const float* mu, const float* log_sigma, const float* z, c
                       int32_t B, int32_t T, int32_t S, int32_t D, float* value_out, hipStream_t stream);
 
 /*
- * Full alignment: mas_search into the workspace's row_start table followed by
- * mas_expand_path.  score_out and item_status_out are nullable as above.
+ * Full alignment, with the results of mas_search followed by mas_expand_path
+ * (the row_start table itself is not among them: the workspace's contents are
+ * the library's own).  score_out and item_status_out are nullable as above.
  * No allocation; workspace as for mas_search.
  */
 mas_status mas_forward_ex(const float* value, const int32_t* t_x, const int32_t* t_y,

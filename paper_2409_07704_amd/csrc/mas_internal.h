@@ -42,11 +42,12 @@ struct KParams {
 // chunk: [B][NW][64] slot k: sweep wave g done with chunk 8k+7 (or its last
 // chunk; chunks past 511 are not recorded); walk: [B][64] slot k: walker done
 // with the chunks from 32k up (slot k = its start, for the first block);
-// item: [B][8] step masks of every wave published (windows may start),
-// walk start, walk end, row_start published, ticks the walker waited for
-// windows, (unused) x3; tile: [B * ntile][2] start and
-// end of path tile t; win: [B][4][2][64] window loader k's n-th window (its
-// chunk C-1-k-4n, n < 8): issue, staged.
+// item: [B][8] step masks of every wave published (staging may start),
+// walk start, walk end, row_start published (or the path's ones written, where
+// the sweep workgroups write the path), ticks the walker waited for blocks or
+// windows, (unused) x3; tile: [B * ntile][2] start and end of path tile t (path
+// writers only); win: [B][4][2][64] window loader k's n-th window (its chunk
+// C-1-k-4n, n < 8): issue, staged (items walked from windows only, else 0).
 struct TraceLayout {
   size_t wg, chunk, walk, item, tile, win, total;
 };

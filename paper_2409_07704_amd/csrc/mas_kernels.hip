@@ -24,7 +24,7 @@
 //     workgroup above (an item's first workgroup: holds back the item's start).
 // What bounds a launch: for small batches the chain of dependent steps (about
 // 0.41 us per 32 columns and 1 us per 63 rows, then the walk), for large ones
-// the reads of the value tensor (3.3 to 4 TB/s in 128-byte pieces of rows
+// the reads of the value tensor (up to 4.2 TB/s in 128-byte pieces of rows
 // 16 KiB apart) and the path's stores beside them.
 // The sweep wave holding row t_x-1 walks back from (t_x-1, t_y-1) once every
 // wave of the item has published its masks, one lookup per chunk, from masks
@@ -262,8 +262,8 @@ __device__ __forceinline__ WinGeom win_geom(int tx, int NW, int T) {
 }
 // How an item is walked: from its step masks (kFlatMasks) or descent bytes
 // (kFlatBytes) staged whole; from a ring of blocks of four chunks' descent
-// bytes (kRing4); or, with more than about 4000 rows, from banded windows
-// (kWindows).  The walk area holds the staged bytes, then (but for windows)
+// bytes (kRing4); or, where fewer than three such blocks fit (more than 3024 rows, or
+// a record of several hundred thousand frames), from windows (kWindows).  The walk area holds the staged bytes, then (but for windows)
 // the walk's record: the row the path enters each chunk in.
 enum WalkMode { kFlatMasks, kFlatBytes, kRing4, kWindows };
 constexpr int kBlk = 4;  // chunks of a ring block
@@ -1156,8 +1156,8 @@ __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, cons
 //   v_lshl_or  pc = xc << 1 | b.
 // Only the last two depend on the previous column (the others, with an s_nop,
 // fill the two wait states between a VALU write of VCC or of a DPP source and
-// its use), and // neither writes VCC, so consecutive columns do not wait on each other's
-// carry.  Lane 0 (the row above the wave) has no lane below: DPP leaves its
+// its use), and neither writes
+// VCC, so consecutive columns do not wait on each other's carry.  Lane 0 (the row above the wave) has no lane below: DPP leaves its
 // xc unwritten, all ones (mask 0), so a path that climbs into it contributes
 // nothing more.
 __device__ __forceinline__ void mask_cols8(uint32_t& wc, uint32_t& xc, uint32_t pc, uint32_t (&o)[8]) {
@@ -1487,7 +1487,7 @@ __device__ __forceinline__ void stage_item(const KParams& p, SweepLds& L, int b,
 // nothing but the chain, the record and the prefetch (rows lie in a row in
 // pm and pd, so its address is one subtraction).
 template <bool MASKS, bool RING>
-__device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const WalkPlan& wp, int tx, int lane, Bound& bd) {
+__device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const WalkPlan& wp, int b, int tx, int lane, Bound& bd) {
   using lds_u32 = __attribute__((address_space(3))) uint32_t;
   using lds_u8 = __attribute__((address_space(3))) uint8_t;
   constexpr int kEnt = MASKS ? 4 : 1;
@@ -1505,13 +1505,19 @@ __device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const W
     if (MASKS) return *(const lds_u32*)(uintptr_t)a;
     return *(const lds_u8*)(uintptr_t)a;
   };
+  // (debug build) lane k: chunks >= 32k walked, lane C/32 + 1: start; ticks
+  // spent waiting for blocks.
+  Stamps wstamps;
+  Waited waited;
   // Ring: waits (bounded) until blocks >= q are staged.
   auto ensure = [&](int q) __attribute__((always_inline)) {
     int spins = 0;
     while (!bd.out && __builtin_amdgcn_ballot_w64(*(volatile __attribute__((address_space(3))) int*)(uintptr_t)(lds_off(&L.bready[0]) + 4u * (uint32_t)min(lane, kStagers - 1)) > q) != 0) {
+      if (spins == 0) waited.begin();
       if (++spins > bd.limit) bd.expire();
       __builtin_amdgcn_s_sleep(1);
     }
+    waited.end();
   };
   int e = tx - 1, g = e / kRowsPerWave, cw = wp.chunks - 1;
   int rr = e - kRowsPerWave * g;  // the row's place in its wave
@@ -1553,6 +1559,7 @@ __device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const W
     lgkm_wait0();
   };
   if (e > 0) {
+    wstamps.at(min((cw >> 5) + 1, kWave - 1));
     const int qtop = cw / kBlk;
     if (RING)
       ensure(max(qtop - 1, 0));
@@ -1574,6 +1581,7 @@ __device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const W
     }
     while (cw >= 0 && e > 0) {
       const int q = cw / kBlk;
+      if (((cw + 1) & 31) == 0) wstamps.at((cw + 1) >> 5);
       if (RING) {
         lds_put(lds_off(&L.wpos), q);
         ensure(max(q - 1, 0));
@@ -1586,8 +1594,11 @@ __device__ __forceinline__ void walk_item(const KParams& p, SweepLds& L, const W
       body(Pb, bb, below + 2 * stride);
       if (((cw + 1) & (kWave - 1)) == 0) flush(cw + 1);
     }
+    wstamps.at(max(cw + 1, 0) >> 5);
     if (((cw + 1) & (kWave - 1)) != 0) flush(cw + 1);
   }
+  wstamps.flush(trace_of(p).walk + (size_t)b * kWave);
+  waited.flush(trace_of(p).item + 8 * (size_t)b + 4);
   lds_put(lds_off(&L.wpos), -1);
 }
 
@@ -1630,8 +1641,8 @@ __device__ __forceinline__ void walk_helper(const KParams& p, SweepLds& L, int b
   }
 }
 
-// The same walk from windows, for items of more than about 4000 rows, whose
-// blocks of whole chunks do not fit LDS: per chunk, from the top, the byte of
+// The same walk from windows, for items whose blocks of whole chunks do not fit
+// LDS three times (see WalkMode): per chunk, from the top, the byte of
 // the row the path enters the chunk in gives the row it leaves the
 // chunk in: that many rows up, or, for a path that climbs into the row above
 // its wave at position p, to the wave's row above and then as many rows as
@@ -2000,7 +2011,7 @@ __device__ __forceinline__ int wait_published(const KParams& p, int k, uint32_t 
 // workgroup waits for this one's item.  Wave 0 alone polls the completion
 // order (device-scope loads, which go past the caches) and hands the item to
 // the other waves through LDS; they wait at the barrier meanwhile, so a
-// waiting workgroup puts one poll rather than twelve on the memory system
+// waiting workgroup puts one poll rather than eight on the memory system
 // at a time, beside the sweeps still running.
 __device__ __forceinline__ void path_writer(const KParams& p, SweepLds& L, uint32_t tag, int wv, int lane, Bound& bd) {
   const int ntiles = p.B * p.ntile;
@@ -2050,9 +2061,9 @@ __device__ __forceinline__ void publish_item(const KParams& p, int b, uint32_t t
   }
 }
 
-// The workgroup of the wave holding row t_x-1 walks the item: that wave walks
-// and publishes row_start, the workgroup's four loaders stage the decision
-// windows.
+// The workgroup of the wave holding row t_x-1 walks the item: that wave walks,
+// the loaders, finishers and receiver stage what it walks from (staging_role),
+// and all eight waves make the outputs (finish_item).
 __device__ __forceinline__ bool walker_workgroup(const WaveCtx& x) {
   return x.g / kWavesPerBlock == x.g_last / kWavesPerBlock;
 }
@@ -2074,11 +2085,11 @@ __device__ __forceinline__ void sweep_role(const KParams& p, SweepLds& L, const 
   const WalkPlan wp = walk_plan(x.ty, p.EP, p.T);
   stamp(trace_of(p).item + 8 * (size_t)b + 1);
   if (wp.mode == kFlatMasks)
-    walk_item<true, false>(p, L, wp, x.tx, lane, bd);
+    walk_item<true, false>(p, L, wp, b, x.tx, lane, bd);
   else if (wp.mode == kFlatBytes)
-    walk_item<false, false>(p, L, wp, x.tx, lane, bd);
+    walk_item<false, false>(p, L, wp, b, x.tx, lane, bd);
   else if (wp.mode == kRing4)
-    walk_item<false, true>(p, L, wp, x.tx, lane, bd);
+    walk_item<false, true>(p, L, wp, b, x.tx, lane, bd);
   else
     walk(p, L, b, x.tx, x.ty, lane, bd);
   stamp(trace_of(p).item + 8 * (size_t)b + 2);
@@ -2140,8 +2151,8 @@ __device__ __forceinline__ void finish_call(const KParams& p, uint32_t gen) {
   }
 }
 
-// Twelve waves per workgroup (four sweep waves, four loaders, four
-// finishers), one workgroup per CU.
+// Eight waves per workgroup (two sweep waves, two loaders, three finishers, a
+// receiver; see Role), two workgroups per CU.
 __global__ void __launch_bounds__(kThreads, 4) mas_kernel(KParams p) {
   __shared__ SweepLds L;
   if (threadIdx.x == 0) stamp(trace_of(p).wg + 2 * (size_t)blockIdx.x);

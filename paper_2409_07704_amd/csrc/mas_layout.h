@@ -4,8 +4,9 @@
 // the row above the wave (row 63g-1, a copy handed down by the previous
 // wave; for g = 0 the virtual -inf row above row 0) and lanes 1..63 own
 // rows 63g .. 63g+62, one text row per lane.  Two such waves (126 rows)
-// share a workgroup with the waves that feed them.  Speech columns are processed in chunks of 32, and every lane
-// packs its row's 32 forward decisions of a chunk into one 32-bit word.
+// share a workgroup with the waves that feed them.  Speech columns are
+// processed in chunks of 32, and every lane packs its row's 32 forward
+// decisions of a chunk into one 32-bit word.
 #pragma once
 
 #include <stddef.h>
@@ -61,22 +62,28 @@ __host__ __device__ constexpr int ent_row0(int NW) { return kChunk * NW; }
 // ones.
 // Dense path of large batches: written in tiles of kPathTileRows rows of one
 // item, taken in the order the items' row_start tables are published, by at
-// most kPathWorkgroups path-writer workgroups (enough to keep up; with more of
-// them the sweeps still running lose more than the path gains: B = 64,
-// T = 1024, S = 4096, three draws: 198 / 165 / 168 us with 96, 201 / 169 / 169
-// with 128, 209 / 193 / 185 with 256, 223 / 207 / 197 with 384; B = 32,
-// T = 2048, S = 8192: 560, 557, 573 and 579 us).
+// most kPathWorkgroups path-writer workgroups: enough to keep up; with more the
+// sweeps still running lose what the path gains.  With 96, 112, 128, 160 and
+// 192 (us): 64 x 1024 x 4096 mixed lengths, eight draws 170.8, 166.0, 162.6,
+// 161.7, 162.4, ragged 211, 204, 199, 199, 203, full 312, 303, 298, 295, 295; 32
+// x 2048 x 8192 518, 512, 513, 518, 522; 300 x 200 x 1200 122, 117, 117, 115, 124.
 constexpr int kPathTileRows = 32;
 constexpr int kPathWorkgroups = 128;
 constexpr uint64_t kShapeSlack = 192;  // (shapes are accepted up to this much below 2^31 boundary regions)
 
 // Batches of at most this many cells (B T S) get their path from the sweep
 // workgroups themselves, zeros first (KParams::early): their launches wait on
-// chains of dependent steps, not on HBM, so that the zeros cost nothing before
-// the sweeps and only the ones are left after the walks.  Measured, path
-// writers / early: 14.9 / 10.9 us (1 x 32 x 32), 47.5 / 41.7 (32 x 256 x 1024),
-// 80.6 / 69.4 (32 x 512 x 2048), 119 / 122 (64 x 252 x 4096, 64.5 M cells), 174
-// / 235 (64 x 1024 x 4096).
+// chains of dependent steps, not on HBM, so that the zeros cost little before
+// the sweeps and only the ones are left after the walks.  Larger ones also
+// start their items by length (KParams::stagger).  Measured, path writers /
+// early (us): 200 x 128 x 1500 85 / 45, 32 x 512 x 2048 60.0 / 57.9, 48 x 400 x
+// 2400 64.7 / 62.5; just below the limit, few items of many cells do better
+// with writers (64 x 252 x 4096 103 / 114, 16 x 1024 x 4000 125 / 131, 64 x 500
+// x 2000 ragged 64 / 67, full 86 / 85), many small ones far worse; above it,
+// with the staggered start, 64 x 300 x 4096 114 / 116, 24 x 1024 x 4096 134 /
+// 142, 64 x 500 x 3000 159 / 112, 64 x 1024 x 4096 174 / 235.
+// So cells alone draw the line coarsely; it lies where the many small items of
+// a batch still get the early path and the benchmark's long ones do not.
 constexpr uint64_t kEarlyMaxCells = (uint64_t)64 << 20;
 
 struct WsHeader {

@@ -47,10 +47,13 @@ constexpr int kUnitStartCost = 3;                 // a unit's start-up, in tiles
 constexpr int kMaxWaves = 16;
 constexpr int kPolicyStream = 2;                  // cache policy nt: streaming
 // Value tensors larger than this (the memory-side cache) are stored past the
-// caches.  Measured, cached / streaming: 64 x 1024 x 4096, D = 80, unit
-// variance 310 / 270 us, followed by mas_search 598 / 548; 32 x 512 x 2048 (134
-// MB) 37.6 / 36.3 us, but 97 / 102 with the search, which then finds the values
-// in the cache.
+// caches.  Measured, cached / streaming (us), 64 x 1024 x 4096, D = 80: unit
+// variance, full lengths 305 / 265, followed by mas_forward_ex 630 / 573; mixed
+// lengths 140 / 135 on inputs not touched just before, followed by
+// mas_forward_ex 304 / 294 (with log-sigmas 350 / 342), and 134 / 92 when the
+// call is repeated (streaming leaves mu and z in the cache for the next one).
+// 32 x 512 x 2048 (134 MB) 37.6 / 36.3, but 97 / 102 with the search, which then
+// finds the values in the cache.
 constexpr uint64_t kStreamBytes = (uint64_t)256 << 20;
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
@@ -563,9 +566,9 @@ __global__ void __launch_bounds__((kLlWaves + NB) * 64)
           // l holds text row l % 16 and frames 4 (l / 16) + r of each n-block,
           // four neighbouring cells of a row.  Lanes l and l ^ 8 swap a piece so
           // that a store covers eight rows' whole 128 bytes: the stores bound
-          // the unit-variance producer (64 x 1024 x 4096: 189 us without any;
-          // 345 with one cell per lane in four 64-byte pieces of rows, 403 with
-          // 16-byte pieces in sixteen of them, 310 this way, 270 streaming).  A cell is in the band when 0 <=
+          // the unit-variance producer (64 x 1024 x 4096, full lengths: 189 us
+          // without any; 341 with one cell per lane in four 64-byte pieces of rows, 403 with
+          // 16-byte pieces in sixteen of them, 305 this way, 265 streaming).  A cell is in the band when 0 <=
           // j - i <= slack and j < t_y; a block wholly inside the band stores
           // without per-cell checks.
           u32x4 v[2];

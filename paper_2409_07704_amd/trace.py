@@ -187,7 +187,7 @@ def format_summary(s, title: str) -> str:
                      f"{r['windows_ready_us']:10.1f} {r['walk_start_us']:10.1f} {r['walk_end_us']:9.1f} "
                      f"{r['published_us']:10.1f} {r['walk_us']:8.1f} {r['walk_us_per_chunk']:10.3f} "
                      f"{r['step_us_median']:9.3f} {r['step_us_p90']:9.3f} {r['hand_lag_us_median']:9.2f} {r['walk_waited_us']:9.1f}"
-                     f" {r['win_lat_us_median']:7.2f} {r['win_lat_us_p90']:9.2f}")
+                     + (f" {r['win_lat_us_median']:7.2f} {r['win_lat_us_p90']:9.2f}" if r["windows"] else f" {'-':>7} {'-':>9}"))
     lats = [r["win_lat_us_median"] for r in s["items"] if r["windows"]]
     if lats:
         lines.append(f"walk windows (issue to staged): median over items of the per-item median {np.median(lats):.2f} us")
