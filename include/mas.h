@@ -50,9 +50,10 @@
  *     lengths live there); they give the item an all-zero slab, score -inf
  *     and a code in item_status_out.
  *   - Alignment: the forward pass uses 16-byte loads whatever S and the
- *     alignment of value (which is that of a float at least).  The path writer
- *     of large batches uses 16-byte stores when S is a multiple of 16 and
- *     path_out is 16-byte aligned, bytes otherwise.
+ *     alignment of value (which is that of a float at least), and writes the
+ *     path by 16-byte stores, with single bytes at the ends of rows that are
+ *     not 16-byte aligned.  mas_expand_path uses 16-byte stores when S is a
+ *     multiple of 16 and path_out is 16-byte aligned, bytes otherwise.
  */
 #ifndef LIBMAS_MAS_H_
 #define LIBMAS_MAS_H_

@@ -29,7 +29,7 @@ struct KParams {
   uint8_t* pd;          // [B][NC][EP] descent bytes (see mas_layout.h)
   int32_t B, T, S, NW, NC, EP, NB, NS;
   int32_t ntile;        // path tiles per item: ceil(T / kPathTileRows)
-  int32_t path16;       // path 16-byte aligned and S % 16 == 0
+  int32_t path16;       // path 16-byte aligned and S % 16 == 0: every row is whole 16-byte pieces
   int32_t early;        // the sweep workgroups write the path themselves, zeros before their sweeps (small batches)
   int32_t stagger;      // items start in the order of their lengths (large batches, see start_delay)
   int32_t spin_limit;   // bound of a device-side wait, in polls without progress

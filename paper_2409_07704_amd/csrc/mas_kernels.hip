@@ -1908,14 +1908,18 @@ __device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const
 // Rows [r0, r1) of the dense path of item b (Sec. 2: the alignment as a 0/1
 // matrix of the input's size) from its published row_start table: row i
 // holds ones at columns [rs[i], rs[i+1]) and zeros elsewhere (rows t_x .. T-1
-// and invalid items: all zeros).  path16: per row, zero pieces by 16-byte
-// stores (the pieces holding ones are skipped: offset past the resource),
-// then the few pieces holding ones; otherwise bytes.  The stores are
-// streaming (nt): the path is written once and never read here, and keeping
-// it out of the caches leaves them to the sweeps still running (a launch on
-// the bench batch took 206 us with cached stores, 179 us with these).  (Bounds are
-// clamped to the row: the table is read back from memory, never trusted
-// blindly.)
+// and invalid items: all zeros).  Per row, zero pieces by 16-byte stores (the
+// pieces holding ones are skipped: offset past the resource), then the few
+// pieces holding ones; a row that does not begin or end on a 16-byte boundary
+// (path16 unset) has up to 15 bytes before and after its pieces, written singly
+// by lanes 0..15 and 16..31.  (All bytes singly, when S is no multiple of 16,
+// kept 128 writers of eight waves at a third of the rate: 600 x 128 x 1000 244
+// us, 199 this way, 64 x 500 x 3000 159 / 107, 40 x 1024 x 4099 228 / 141, 2 x
+// 8000 x 8100 432 / 374.)  The stores are streaming (nt): the path is written
+// once and never read here, and keeping it out of the caches leaves them to the
+// sweeps still running (a launch on the bench batch took 206 us with cached
+// stores, 179 us with these).  (Bounds are clamped to the row: the table is
+// read back from memory, never trusted blindly.)
 __device__ __forceinline__ void write_path_rows(const KParams& p, int b, int r0, int r1, int lane) {
   const uint32_t* const rs = reinterpret_cast<const uint32_t*>(p.row_start) + (size_t)b * ((size_t)p.T + 1);
   uint8_t* const item_path = p.path + (size_t)b * (size_t)p.T * (size_t)p.S;
@@ -1930,16 +1934,20 @@ __device__ __forceinline__ void write_path_rows(const KParams& p, int b, int r0,
       const int e = k2 + 1 < kWave ? __builtin_amdgcn_readlane(v, k2 + 1) : vlast;
       const int lo = min(max(a, 0), p.S), hi = min(max(e, lo), p.S);
       const int row = i0 + k2;
-      if (p.path16) {
-        const int plo = lo >> 4, phi = hi > lo ? (hi + 15) >> 4 : plo;  // pieces holding ones
-        for (int pc = lane; pc < p.S / 16; pc += kWave)
-          __builtin_amdgcn_raw_buffer_store_b128(zero, r, (pc < plo || pc >= phi) ? row * p.S + 16 * pc : -1, 0, kPolicyStream);
-        for (int pc = plo + lane; pc < phi; pc += kWave)
-          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, path_piece(lo, hi, 16 * pc)), r, row * p.S + 16 * pc, 0,
-                                                 kPolicyStream);
-      } else {
-        uint8_t* const rowp = item_path + (size_t)row * p.S;
-        for (int j = lane; j < p.S; j += kWave) rowp[j] = (uint8_t)(j >= lo && j < hi);
+      // The row's 16-byte pieces begin at the first 16-byte boundary in it.
+      const int head = p.path16 ? 0 : min((int)(-(uintptr_t)(item_path + (size_t)row * p.S) & 15), p.S);
+      const int np = (p.S - head) / 16, at = row * p.S + head, l = lo - head, h = hi - head;
+      const int plo = min(max(l, 0) >> 4, np), phi = h > max(l, 0) ? min((h + 15) >> 4, np) : plo;  // pieces holding ones
+      for (int pc = lane; pc < np; pc += kWave)
+        __builtin_amdgcn_raw_buffer_store_b128(zero, r, (pc < plo || pc >= phi) ? at + 16 * pc : -1, 0, kPolicyStream);
+      for (int pc = plo + lane; pc < phi; pc += kWave)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, path_piece(l, h, 16 * pc)), r, at + 16 * pc, 0,
+                                               kPolicyStream);
+      if (!p.path16) {
+        // The bytes before the first piece (lanes 0 .. 15) and after the last one (16 .. 31).
+        const int j = lane < 16 ? lane : head + 16 * np + lane - 16;
+        const bool in = lane < 16 ? lane < head : lane < 32 && j < p.S;
+        __builtin_amdgcn_raw_buffer_store_b8((uint8_t)(j >= lo && j < hi), r, in ? row * p.S + j : -1, 0, 0);
       }
     }
   }

@@ -72,6 +72,40 @@ def test_routes(B, T, S, lengths, shift):
     assert np.array_equal(rs.cpu().numpy()[:, 1:] - rs.cpu().numpy()[:, :-1], dur.cpu().numpy())
 
 
+@pytest.mark.parametrize("B,T,S,shift", [
+    (16, 1010, 4160, 1),    # whole pieces, all of them off a boundary
+    (16, 1010, 4171, 0),    # every row at another place between boundaries
+    (16, 1010, 4171, 3),
+    (70_000, 31, 33, 0),    # two or one pieces a row
+    (440_000, 12, 13, 5),   # rows of less than a piece
+])
+def test_path_writers_unaligned(B, T, S, shift):
+    """The path writers' pieces and single bytes, in batches of more cells than
+    the sweep workgroups write: every byte against the oracle, with bytes on
+    both sides of the path left alone."""
+    import paper_2409_07704_amd as mas
+
+    rng = np.random.default_rng(B + S + shift)
+    tx = rng.integers(1, T + 1, B).astype(np.int32)
+    ty = rng.integers(tx, S + 1).astype(np.int32)
+    tx[0], ty[0], tx[1] = T, S, 0
+    value, tx, ty = synth.normal_batch(B, T, S, tx, ty, seed=S)
+    print(f"[gpu-case] path writers B={B} T={T} S={S} shift={shift}", flush=True)
+    op, os_, ost = oracle.mas(value, tx, ty)
+    n = value.size
+    assert n > 64 << 20
+    v, x, y = (torch.from_numpy(a).cuda() for a in (value, tx, ty))
+    raw = torch.full((n + 64,), 0xA5, dtype=torch.uint8, device="cuda")
+    path = raw[16 + shift : 16 + shift + n].view(B, T, S)
+    status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+    mas.mas_forward_ex(v, x, y, path, None, status, workspace=mas.Workspace(B, T, S))
+    torch.cuda.synchronize()
+    assert np.array_equal(status.cpu().numpy(), ost)
+    assert np.array_equal(path.cpu().numpy(), op)
+    edge = raw.cpu().numpy()
+    assert (edge[: 16 + shift] == 0xA5).all() and (edge[16 + shift + n :] == 0xA5).all()
+
+
 def test_more_workgroups_than_a_grid_holds():
     """4.3 M items of 127 padded rows: two workgroups each, more threads than one
     launch can have.  One-token items have closed-form results."""
