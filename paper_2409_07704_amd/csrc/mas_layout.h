@@ -76,14 +76,13 @@ constexpr uint64_t kShapeSlack = 192;  // (shapes are accepted up to this much b
 // chains of dependent steps, not on HBM, so that the zeros cost little before
 // the sweeps and only the ones are left after the walks.  Larger ones also
 // start their items by length (KParams::stagger).  Measured, path writers /
-// early (us): 200 x 128 x 1500 85 / 45, 32 x 512 x 2048 60.0 / 57.9, 48 x 400 x
-// 2400 64.7 / 62.5; just below the limit, few items of many cells do better
-// with writers (64 x 252 x 4096 103 / 114, 16 x 1024 x 4000 125 / 131, 64 x 500
-// x 2000 ragged 64 / 67, full 86 / 85), many small ones far worse; above it,
-// with the staggered start, 64 x 300 x 4096 114 / 116, 24 x 1024 x 4096 134 /
-// 142, 64 x 500 x 3000 159 / 112, 64 x 1024 x 4096 174 / 235.
-// So cells alone draw the line coarsely; it lies where the many small items of
-// a batch still get the early path and the benchmark's long ones do not.
+// early (us): 200 x 128 x 1500 65 / 45, 32 x 512 x 2048 60 / 58, 48 x 400 x 2400
+// 64 / 62, 64 x 500 x 2000 64 / 65, 16 x 1024 x 4000 125 / 131, 64 x 252 x 4096
+// 104 / 113 (the last three just below the limit); above it 300 x 200 x 1200 115
+// / 83, 600 x 128 x 1000 200 / 175, 64 x 300 x 4096 113 / 114, 64 x 500 x 3000
+// 107 / 112, 24 x 1024 x 4096 132 / 138, 64 x 1024 x 4096 162 / 218.  So cells
+// alone draw the line coarsely: items of many cells would have it a fifth lower,
+// batches of many small ones above 128 M.
 constexpr uint64_t kEarlyMaxCells = (uint64_t)64 << 20;
 
 struct WsHeader {
