@@ -899,13 +899,14 @@ __device__ __forceinline__ float sweep_wave(const KParams& p, SweepLds& L, const
 // Estimates are in wall-clock ticks (100 MHz): kTicksPerChunk per 32
 // columns (about one chunk step of a sweep wave in a full batch) and
 // kTicksPerGroup per 63 rows, chosen by timing full batches of mixed lengths
-// (five draws of B = 64, T = 1024, S = 4096: 168 us on average, against 170
-// to 174 us with 85 / 100, 60 / 200, 120 / 180 or 130 / 130 ticks).  Small batches (KParams::stagger)
-// start at once: they do not fill HBM, and a delay made from a full batch's
-// steps would turn short items into the last ones (32 x 256 x 1024, ragged:
-// 38.9 us with delays, 33.5 us without).  Batches larger than kDelayMaxBatch start
-// at once (every workgroup would read every length), and no delay exceeds
-// kDelayMaxTicks (1 ms, far below the bound of any device-side wait).
+// (eight draws of B = 64, T = 1024, S = 4096: 163 us on average, against 164,
+// 170, 169 and 171 us with 85 / 100, 60 / 200, 120 / 180 and 130 / 130 ticks).
+// Small batches (KParams::stagger) start at once: they do not fill HBM, and a
+// delay made from a full batch's steps would turn short items into the last
+// ones (32 x 512 x 2048, ragged: 68 us with delays, 58 without).  Batches larger
+// than kDelayMaxBatch start at once (every workgroup would read every length),
+// and no delay exceeds kDelayMaxTicks (1 ms, far below the bound of any
+// device-side wait).
 constexpr int kTicksPerChunk = 110;
 constexpr int kTicksPerGroup = 130;
 constexpr int kDelayPercent = 80;
