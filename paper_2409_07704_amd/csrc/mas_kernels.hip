@@ -1157,9 +1157,9 @@ __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, cons
 //   v_lshl_or  pc = xc << 1 | b.
 // Only the last two depend on the previous column (the others, with an s_nop,
 // fill the two wait states between a VALU write of VCC or of a DPP source and
-// its use), and neither writes
-// VCC, so consecutive columns do not wait on each other's carry.  Lane 0 (the row above the wave) has no lane below: DPP leaves its
-// xc unwritten, all ones (mask 0), so a path that climbs into it contributes
+// its use), and neither writes VCC, so consecutive columns do not wait on each
+// other's carry.  Lane 0 (the row above the wave) has no lane below: DPP leaves
+// its xc unwritten, all ones (mask 0), so a path that climbs into it contributes
 // nothing more.
 __device__ __forceinline__ void mask_cols8(uint32_t& wc, uint32_t& xc, uint32_t pc, uint32_t (&o)[8]) {
   uint32_t b0, b1;
@@ -2156,7 +2156,7 @@ __device__ __forceinline__ void finish_call(const KParams& p, uint32_t gen) {
       __hip_atomic_store(&p.hdr->walk_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&p.hdr->tile_next, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(&p.hdr->exit_count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(&p.hdr->gen, gen + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&p.hdr->gen, gen + 1u < kGenEnd ? gen + 1u : 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
 }

@@ -85,8 +85,12 @@ constexpr uint64_t kShapeSlack = 192;  // (shapes are accepted up to this much b
 // batches of many small ones above 128 M.
 constexpr uint64_t kEarlyMaxCells = (uint64_t)64 << 20;
 
+// Generations run from 0 to kGenEnd - 1 and start over: a call's tags, 2 gen + 1
+// and 2 gen + 2, are never 0, which is what a clear workspace and a load that
+// was dropped hold.
+constexpr uint32_t kGenEnd = 0x7fffffffu;
 struct WsHeader {
-  uint32_t gen;         // call generation; tag of a call = 2 * gen + 1
+  uint32_t gen;         // call generation; tag of a call = 2 * gen + 1 (and the even number after it, see slot_region)
   uint32_t exit_count;  // workgroups that finished the current call
   uint32_t error;       // sticky: non-zero once a device-side wait timed out
   uint32_t walk_count;  // row_start tables published in the current call

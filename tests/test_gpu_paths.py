@@ -72,6 +72,39 @@ def test_routes(B, T, S, lengths, shift):
     assert np.array_equal(rs.cpu().numpy()[:, 1:] - rs.cpu().numpy()[:, :-1], dur.cpu().numpy())
 
 
+@pytest.mark.parametrize("B,T,S", [(2, 505, 1999), (17, 1010, 4160)])
+def test_generation_starts_over(B, T, S):
+    """The last generations of a workspace and the first ones after them: no tag
+    of a call is 0, the value of the boundary words of a clear workspace (items
+    of five and nine workgroups, which use both tags of a call; a small batch
+    and one with narrow polls)."""
+    import paper_2409_07704_amd as mas
+
+    tx = np.array([T - 5 * (b % 16) for b in range(B)], np.int32)
+    ty = np.array([S - 37 * b for b in range(B)], np.int32)
+    value, tx, ty = synth.normal_batch(B, T, S, tx, ty, seed=S)
+    print(f"[gpu-case] generation starts over B={B} T={T} S={S}", flush=True)
+    op, os_, ost = oracle.mas(value, tx, ty)
+    v, x, y = (torch.from_numpy(a).cuda() for a in (value, tx, ty))
+    ws = mas.Workspace(B, T, S)
+    off = ws.ptr - ws._buf.data_ptr()
+    gen = ws._buf[off : off + 4].view(torch.int32)
+    assert gen.item() == 0
+    gen.fill_(0x7FFFFFFD)
+    seen = []
+    for _ in range(4):
+        path = torch.full((B, T, S), 0xA5, dtype=torch.uint8, device="cuda")
+        score = torch.full((B,), 3.0, device="cuda")
+        status = torch.full((B,), -1, dtype=torch.int32, device="cuda")
+        mas.mas_forward_ex(v, x, y, path, score, status, workspace=ws)
+        torch.cuda.synchronize()
+        seen.append(gen.item())
+        assert np.array_equal(status.cpu().numpy(), ost)
+        assert score.cpu().numpy().tobytes() == os_.tobytes()
+        assert np.array_equal(path.cpu().numpy(), op)
+    assert seen == [0x7FFFFFFE, 0, 1, 2]
+
+
 @pytest.mark.parametrize("B,T,S,shift", [
     (16, 1010, 4160, 1),    # whole pieces, all of them off a boundary
     (16, 1010, 4171, 0),    # every row at another place between boundaries
