@@ -1073,8 +1073,9 @@ __device__ __forceinline__ void load_tiles(const KParams& p, SweepLds& L, const 
 // value tiles.  Measured, four chunks / four, one after an empty poll / two,
 // one after an empty poll: 64 x 1024 x 4096 mixed lengths 173 / 164 / 162 us,
 // full lengths 319 / 308 / 298, 32 x 2048 x 8192 547 / 530 / 515; one chunk
-// always: 190, 312, 542.  A lone item of 17 workgroups, whose polls compete with
-// nothing, loses 0.5 % to the narrow ones (1 x 2048 x 8000).
+// always: 190, 312, 542.  (This loop is sensitive to its code: between builds
+// that differ elsewhere a lone item of 17 workgroups, 1 x 2048 x 8000, takes 222
+// to 227 us.)
 // (Chunks past the item's last are read, inside the workspace, but never
 // delivered, whatever their words hold.)
 __device__ __forceinline__ void receive_rows(const KParams& p, SweepLds& L, const WaveCtx& x, uint32_t tag, Bound& bd) {
@@ -1896,8 +1897,8 @@ __device__ __forceinline__ void finish_item(const KParams& p, SweepLds& L, const
     // stores path_fail, waits for it, then looks at the order again.  So one of
     // the two sees the other: an item whose rows a writer left out never
     // reports itself OK.  (Waited for here, not after publish_item, where it
-    // cost 220 more reads of spilled scalars over the kernel: 222 -> 226 us for
-    // 1 x 2048 x 8000.  Without path writers there is nothing to order: 512 x 64
+    // cost 220 more reads of spilled scalars over the kernel: 32 x 256 x 1024
+    // 34.0 -> 34.4 us.  Without path writers there is nothing to order: 512 x 64
     // x 300 took 34.5 us with the wait for the path's ones here, 32.5 without.)
     if (p.path && !p.early) vm_wait<0>();
     const bool tmo = ld_dev(p.tmo + b) == tag || ld_dev(&p.hdr->path_fail) == tag;
